@@ -19,8 +19,8 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libdptq.so")
 
-SOURCES = ["dptq_api.hip", "rotate_quant.hip", "qgemm.hip", "qgemm_fp6.hip", "decode_fused.hip", "kv_quant.hip",
-           "range_quant.hip"]
+SOURCES = ["rotate_quant.hip", "decode_fused.hip", "qgemm_ksplit.hip", "range_quant.hip", "qgemm.hip", "qgemm_fp6.hip",
+           "kv_quant.hip", "dptq_api.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [
@@ -50,7 +50,7 @@ def _run(cmd, verbose):
         print(out, flush=True)
 
 
-def build(verbose=False, jobs=4):
+def build(verbose=False, jobs=8):
     """Compile every source and link libdptq.so; returns the library path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     hipcc = _hipcc()

@@ -47,8 +47,32 @@ hipError_t launch_kv_quant(const void* kv, int64_t T, int64_t D, int group, uint
 hipError_t launch_kv_dequant(const uint8_t* codes, const float* scales, const float* mins,
                              int64_t T, int64_t D, int group, void* out, hipStream_t stream);
 
-// GEMM kernels (values of dptq_gemm_kernel).
-constexpr int kGemmAuto = 0, kGemmDecode = 1, kGemmTile = 2, kGemmWide = 3;
+// GEMM kernels (values of dptq_gemm_kernel, then kGemmKsplit: the K-split
+// kernel that serves kGemmDecode, at any M).
+constexpr int kGemmAuto = 0, kGemmDecode = 1, kGemmTile = 2, kGemmWide = 3, kGemmKsplit = 4;
+
+// One call of the K-split GEMM (qgemm_ksplit.hip): y from the dequant epilogue,
+// with the zero-point correction when a_zeros is given, or the raw
+// accumulators when acc is.
+struct KsplitCall {
+  const uint8_t* a;
+  const float* a_scales;
+  int64_t M;
+  int K;
+  const uint8_t* w;
+  const float* w_scales;
+  int64_t N;
+  __half* y;
+  int32_t* acc;
+  const int32_t* a_zeros;
+  const int32_t* w_sums;
+};
+// Weight layouts: canonical nibbles (any output), the 8-bit activation order
+// (bits 8, y), the decode layout (M <= 16, y or acc).
+constexpr int kWeightsCanonical = 0, kWeightsA8Order = 2, kWeightsDecode = 3;
+hipError_t launch_ksplit(const KsplitCall& c, int bits, int weights, hipStream_t stream);
+// Estimated microseconds of its best tile for M > 16.
+double ksplit_cost(int64_t M, int64_t N, int K, int bits);
 
 // Whether a kernel covers the shape (kGemmAuto and kGemmTile cover all).
 bool gemm_kernel_fits(int kernel, int64_t M, int64_t N, int K, int bits);

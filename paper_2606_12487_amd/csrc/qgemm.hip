@@ -22,103 +22,12 @@
 
 #include "dptq.h"
 #include "internal.h"
+#include "qgemm_device.h"
 
 namespace dptq {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint32_t nib_lo(uint32_t v) { return (v << 4) & 0xF0F0F0F0u; }
-__device__ __forceinline__ uint32_t nib_hi(uint32_t v) { return v & 0xF0F0F0F0u; }
-
-// Even-k bytes of an 8-byte run (d0 = k0..3, d1 = k4..7): [k0, k2, k4, k6].
-__device__ __forceinline__ uint32_t even_bytes(uint32_t d0, uint32_t d1) {
-  return __builtin_amdgcn_perm(d1, d0, 0x06040200u);
-}
-// Odd-k bytes: [k1, k3, k5, k7].
-__device__ __forceinline__ uint32_t odd_bytes(uint32_t d0, uint32_t d1) {
-  return __builtin_amdgcn_perm(d1, d0, 0x07050301u);
-}
-
-// MFMA operand for one 64-k step from two packed 4-bit dwords (k 0..7, 8..15
-// of this lane's 16-k slice).
-__device__ __forceinline__ v4i op_from_nibbles(uint32_t v0, uint32_t v1) {
-  v4i r;
-  r.x = (int)nib_lo(v0);
-  r.y = (int)nib_hi(v0);
-  r.z = (int)nib_lo(v1);
-  r.w = (int)nib_hi(v1);
-  return r;
-}
-// Same k order from 16 int8 codes d0..d3 (k 0..15).
-__device__ __forceinline__ v4i op_from_bytes(uint32_t d0, uint32_t d1, uint32_t d2, uint32_t d3) {
-  v4i r;
-  r.x = (int)even_bytes(d0, d1);
-  r.y = (int)odd_bytes(d0, d1);
-  r.z = (int)even_bytes(d2, d3);
-  r.w = (int)odd_bytes(d2, d3);
-  return r;
-}
-
-// 8-bit activation operand of one 32-k step.  Against weights in the
-// canonical nibble order the activation bytes are regrouped like the nibble
-// unpack (even k, then odd k).  Weights in the 8-bit order (each dword holds
-// k0..k3 in its low nibbles and k4..k7 in its high ones, pack_w4_a8_kernel)
-// unpack to natural k order, so the activation dwords are the operand as
-// they stand.
-template <bool WA8>
-__device__ __forceinline__ v4i op_a8(uint32_t d0, uint32_t d1, uint32_t d2, uint32_t d3) {
-  if constexpr (WA8) {
-    v4i r;
-    r.x = (int)d0;
-    r.y = (int)d1;
-    r.z = (int)d2;
-    r.w = (int)d3;
-    return r;
-  } else {
-    return op_from_bytes(d0, d1, d2, d3);
-  }
-}
-
-__device__ __forceinline__ v4i mfma(v4i a, v4i b, v4i c) {
-  return __builtin_amdgcn_mfma_i32_16x16x64_i8(a, b, c, 0, 0, 0);
-}
-
-template <int BITS>
-__device__ __forceinline__ int unscale(int v) { return BITS == 4 ? (v >> 8) : (v >> 4); }
-
-// fl16(fl32(fl32(fl32(acc) * as) * ws)).  The empty asm pins t2 as an fp32
-// value: without it the backend folds the last multiply and the fp16
-// conversion into one mixed-precision FMA (a single rounding to fp16), which
-// differs from the two roundings the epilogue is defined with.
-__device__ __forceinline__ __half dequant(int acc, float as, float ws) {
-  const float t0 = (float)acc;
-  const float t1 = t0 * as;
-  float t2 = t1 * ws;
-  asm("" : "+v"(t2));
-  return __float2half_rn(t2);
-}
-
-// Four accumulators of one lane (rows n .. n+3 of one column m), unscaled,
-// with the zero-point correction off * wz when ZP, dequantized and packed as
-// fp16.
-template <int BITS, bool ZP>
-__device__ __forceinline__ uint2 dequant4z(int a0, int a1, int a2, int a3, float as, float4 ws,
-                                           int off, int4 wz) {
-  int c0 = unscale<BITS>(a0), c1 = unscale<BITS>(a1), c2 = unscale<BITS>(a2), c3 = unscale<BITS>(a3);
-  if constexpr (ZP) {
-    c0 += off * wz.x;
-    c1 += off * wz.y;
-    c2 += off * wz.z;
-    c3 += off * wz.w;
-  }
-  const __half h0 = dequant(c0, as, ws.x), h1 = dequant(c1, as, ws.y);
-  const __half h2 = dequant(c2, as, ws.z), h3 = dequant(c3, as, ws.w);
-  uint2 pk;
-  pk.x = (uint32_t)__half_as_ushort(h0) | ((uint32_t)__half_as_ushort(h1) << 16);
-  pk.y = (uint32_t)__half_as_ushort(h2) | ((uint32_t)__half_as_ushort(h3) << 16);
-  return pk;
-}
+using namespace qg;
 
 // ---------------------------------------------------------------------------
 // Prefill.  An output tile of BN (n) x BM (m) is computed by WN x WM
@@ -190,12 +99,6 @@ __device__ __forceinline__ v16i mfma32(v4i a, v4i b, v16i c) {
 // distinct banks: rows of 8 chunks (128 B) and of 16 chunks (256 B).
 __device__ __forceinline__ int swz8(int r) { return (r ^ (r >> 3)) & 7; }
 __device__ __forceinline__ int swz16(int r) { return r & 15; }
-
-__device__ __forceinline__ int xcd_remap(int bid, int total) {
-  const int per = total >> 3, rem = total & 7;
-  const int x = bid & 7, idx = bid >> 3;
-  return x * per + (x < rem ? x : rem) + idx;
-}
 
 // Tile (tm, tn) of logical tile `logical`: logical tiles run in groups of
 // kGroupM tile rows, m fastest within a group, so that the tiles an XCD works
@@ -988,175 +891,6 @@ qgemm_prefill_wide(const uint8_t* __restrict__ a_codes, const float* __restrict_
   wait_vmcnt<0>();   // the re-issued tail loads land before the workgroup's LDS is released
 }
 
-// ---------------------------------------------------------------------------
-// Decode (M <= 16): one workgroup per NB blocks of 16 output channels; its 8
-// wavefronts split K, stream the weight rows once with 16-byte loads, and
-// the int32 partial tiles are summed exactly in LDS.  Every workgroup reads
-// all M activation rows of its K range, so when those rows are as many bytes
-// as its weights two blocks share them (NB = 2).
-// ---------------------------------------------------------------------------
-constexpr int kDecWaves = 8;
-constexpr int kDecBatch = 4;
-
-// ZP: the range quantizer's zero-point correction in the epilogue,
-// acc + (2^(BITS-1) - a_zeros[m]) * w_sums[n] (exact int32), before the
-// dequantization.  WDEC: weights in the decode layout (below), where the
-// 16 rows x 64 bytes of a block's 128-k chunk are one contiguous KiB in lane
-// order, so each load instruction streams 1 KiB instead of 16 runs of 64
-// bytes 8 K bytes apart.
-// BATCH: chunks per wavefront in flight (kDecBatch, or 8 where a wavefront
-// streams many chunks and the grid is at most one workgroup per compute
-// unit: decode_batch).
-template <int BITS, bool ACC_OUT, bool ZP = false, bool WA8 = false, int NB = 1, bool WDEC = false,
-          int BATCH = kDecBatch>
-__global__ void __launch_bounds__(kDecWaves * 64)
-qgemm_decode(const uint8_t* __restrict__ a_codes, const float* __restrict__ a_scales,
-             const uint8_t* __restrict__ w_packed, const float* __restrict__ w_scales,
-             int M, int N, int K, __half* __restrict__ y, int32_t* __restrict__ acc_out,
-             const int32_t* __restrict__ a_zeros = nullptr,
-             const int32_t* __restrict__ w_sums = nullptr) {
-  static_assert(NB == 1 || NB == 2, "blocks per workgroup");
-  __shared__ v4i part[NB][kDecWaves][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n0 = blockIdx.x * 16 * NB;
-  const int fr = lane & 15, fg = lane >> 4;
-  const int nck = K / 128;
-  const int c_begin = (int)((long)nck * wave / kDecWaves);
-  const int c_end = (int)((long)nck * (wave + 1) / kDecWaves);
-  const bool mvalid = fr < M;
-
-  const size_t wrow = (size_t)K / 2;
-  // Chunk ck of weight block nb (16 rows) at wp + nb * 16 * wrow + ck * kChunk.
-  constexpr size_t kChunk = WDEC ? 1024 : 64;
-  const uint8_t* wp = WDEC ? w_packed + (size_t)n0 * wrow + lane * 16
-                           : w_packed + (size_t)(n0 + fr) * wrow + fg * 16;
-  const size_t arow = BITS == 4 ? (size_t)K / 2 : (size_t)K;
-  const uint8_t* ap = a_codes + (size_t)(mvalid ? fr : 0) * arow + (BITS == 4 ? fg * 16 : fg * 32);
-
-  v4i acc[NB];
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) acc[nb] = v4i{0, 0, 0, 0};
-  for (int c = c_begin; c < c_end; c += BATCH) {
-    uint4 wv[NB][BATCH], av[BATCH], av2[BATCH];
-#pragma unroll
-    for (int b = 0; b < BATCH; ++b) {
-      const int ck = c + b;
-      const bool ok = ck < c_end;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        wv[nb][b] = ok ? *reinterpret_cast<const uint4*>(wp + (size_t)nb * 16 * wrow + (size_t)ck * kChunk)
-                       : make_uint4(0, 0, 0, 0);
-      if (BITS == 4) {
-        av[b] = (ok && mvalid) ? *reinterpret_cast<const uint4*>(ap + (size_t)ck * 64)
-                               : make_uint4(0, 0, 0, 0);
-      } else {
-        av[b] = (ok && mvalid) ? *reinterpret_cast<const uint4*>(ap + (size_t)ck * 128)
-                               : make_uint4(0, 0, 0, 0);
-        av2[b] = (ok && mvalid) ? *reinterpret_cast<const uint4*>(ap + (size_t)ck * 128 + 16)
-                                : make_uint4(0, 0, 0, 0);
-      }
-    }
-#pragma unroll
-    for (int b = 0; b < BATCH; ++b) {
-      v4i b0, b1;
-      if (BITS == 4) {
-        b0 = op_from_nibbles(av[b].x, av[b].y);
-        b1 = op_from_nibbles(av[b].z, av[b].w);
-      } else {
-        b0 = op_a8<WA8>(av[b].x, av[b].y, av[b].z, av[b].w);
-        b1 = op_a8<WA8>(av2[b].x, av2[b].y, av2[b].z, av2[b].w);
-      }
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        acc[nb] = mfma(op_from_nibbles(wv[nb][b].x, wv[nb][b].y), b0, acc[nb]);
-        acc[nb] = mfma(op_from_nibbles(wv[nb][b].z, wv[nb][b].w), b1, acc[nb]);
-      }
-    }
-  }
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) part[nb][wave][lane] = acc[nb];
-  __syncthreads();
-  // Wavefront nb < NB sums and writes block nb.
-  if (wave >= NB) return;
-  v4i tot = part[wave][0][lane];
-#pragma unroll
-  for (int w = 1; w < kDecWaves; ++w) {
-    const v4i p = part[wave][w][lane];
-    tot.x += p.x; tot.y += p.y; tot.z += p.z; tot.w += p.w;
-  }
-  if (!mvalid) return;
-  const int m = fr, n = n0 + wave * 16 + fg * 4;
-  int c0 = unscale<BITS>(tot.x), c1 = unscale<BITS>(tot.y);
-  int c2 = unscale<BITS>(tot.z), c3 = unscale<BITS>(tot.w);
-  if constexpr (ZP) {
-    const int off = (1 << (BITS - 1)) - a_zeros[m];
-    const int4 ws = *reinterpret_cast<const int4*>(w_sums + n);
-    c0 += off * ws.x;
-    c1 += off * ws.y;
-    c2 += off * ws.z;
-    c3 += off * ws.w;
-  }
-  if (ACC_OUT) {
-    *reinterpret_cast<int4*>(acc_out + (size_t)m * N + n) = make_int4(c0, c1, c2, c3);
-  } else {
-    const float as = a_scales[m];
-    const float4 wsv = *reinterpret_cast<const float4*>(w_scales + n);
-    const __half h0 = dequant(c0, as, wsv.x), h1 = dequant(c1, as, wsv.y);
-    const __half h2 = dequant(c2, as, wsv.z), h3 = dequant(c3, as, wsv.w);
-    uint2 pk;
-    pk.x = (uint32_t)__half_as_ushort(h0) | ((uint32_t)__half_as_ushort(h1) << 16);
-    pk.y = (uint32_t)__half_as_ushort(h2) | ((uint32_t)__half_as_ushort(h3) << 16);
-    *reinterpret_cast<uint2*>(y + (size_t)m * N + n) = pk;
-  }
-}
-
-// Blocks of 16 output channels per decode workgroup.  A one-block workgroup
-// reads M * K * bits / 8 activation bytes beside 8 K weight bytes; once the
-// activations are as large (M * bits >= 64) two blocks share them, provided
-// N still gives two workgroups per compute unit.  (Four blocks were slower
-// at 8 tokens and 4 bits on the 57344-channel shape: measured.)
-int decode_blocks(int64_t M, int64_t N, int bits, int cus) {
-  if (M * bits >= 64 && N % 32 == 0 && N / 32 >= 2 * (int64_t)cus) return 2;
-  return 1;
-}
-
-// Eight chunks in flight instead of four: measured faster (graph-replayed,
-// decode layout) where a wavefront streams at least 12 chunks, the grid is at
-// most one workgroup per compute unit and M <= 4 (LLaMA-3-8B down, K = 14336,
-// N = 4096: M = 1 A4 7.90 -> 7.25 us, M = 4 A4 8.30 -> 7.40 us, M = 1 A8
-// 8.60 -> 8.35 us), and slower with fewer chunks or more workgroups (K = 4096,
-// N = 12288, M = 1: 6.53 -> 8.25 us; K = 8192, N = 57344, M = 8: 43.4 ->
-// 48.0 us at A8).
-bool decode_batch8(int64_t M, int K, int64_t N, int cus) {
-  return M <= 4 && K / 128 >= 12 * kDecWaves && N / 16 <= cus;
-}
-
-template <int BITS, bool ACC_OUT, bool WA8, bool ZP, bool WDEC = false>
-void launch_decode(const uint8_t* a, const float* as, int64_t M, int K, const uint8_t* w,
-                   const float* ws, int64_t N, __half* y, int32_t* acc, const int32_t* az,
-                   const int32_t* wsum, hipStream_t stream) {
-  const int cus = device_cus();
-  const int nb = decode_blocks(M, N, BITS, cus);
-  if (nb == 1 && decode_batch8(M, K, N, cus)) {
-    hipLaunchKernelGGL((qgemm_decode<BITS, ACC_OUT, ZP, WA8, 1, WDEC, 8>), dim3((unsigned)(N / 16)),
-                       dim3(kDecWaves * 64), 0, stream, a, as, w, ws, (int)M, (int)N, K, y, acc, az,
-                       wsum);
-    return;
-  }
-  switch (nb) {
-    case 2:
-      hipLaunchKernelGGL((qgemm_decode<BITS, ACC_OUT, ZP, WA8, 2, WDEC>), dim3((unsigned)(N / 32)),
-                         dim3(kDecWaves * 64), 0, stream, a, as, w, ws, (int)M, (int)N, K, y, acc,
-                         az, wsum);
-      break;
-    default:
-      hipLaunchKernelGGL((qgemm_decode<BITS, ACC_OUT, ZP, WA8, 1, WDEC>), dim3((unsigned)(N / 16)),
-                         dim3(kDecWaves * 64), 0, stream, a, as, w, ws, (int)M, (int)N, K, y, acc,
-                         az, wsum);
-      break;
-  }
-}
-
 // Canonical 4-bit weights [N, K/2] -> the decode layout: block b of 16 rows,
 // chunk c of 128 k, piece g of 16 bytes, row r of the block -> the 16 bytes
 // at ((b * (K / 128) + c) * 4 + g) * 256 + r * 16, copied from row 16 b + r,
@@ -1229,19 +963,39 @@ bool wide_fits(int64_t M, int64_t N, int K) {
   return M >= W::kBM && N >= W::kBN && K >= W::kMinK;
 }
 
+// Estimated microseconds of a tile kernel: a start, then per round of one tile
+// per compute unit its k loop (slower when every unit is busy: power) and its
+// epilogue.  Fitted to measured times over M 17-1024, N 1024-28672, K
+// 2048-14336, within 4%.
+double tile_kernel_us(int64_t M, int64_t N, int K, int bits, bool wide, int cus) {
+  const int64_t bm = wide ? 256 : 128, bn = wide ? 192 : 256;
+  const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
+  const double rounds = (double)((tiles + cus - 1) / cus), k = (double)K;
+  const double fill = tiles < cus ? (double)tiles / cus : 1.0;
+  if (bits == 4)
+    return wide ? 3.0 + rounds * (5.85 + k * (5.81e-3 + 1.43e-3 * fill))
+                : 1.8 + rounds * (4.35 + k * (5.12e-3 + 0.87e-3 * fill));
+  return wide ? 3.9 + rounds * (5.0 + k * (5.55e-3 + 2.17e-3 * fill))
+              : 1.4 + rounds * (4.76 + k * (4.59e-3 + 1.45e-3 * fill));
+}
+
 // Kernel for a shape: M <= 16 streams the weights; otherwise the tile shape
 // with the smaller estimated time (the wide tiles need at least one full
-// tile and a ring's worth of k).
+// tile and a ring's worth of k), or the K-split kernel where that is estimated
+// at least 8% faster still (its estimate is the less exact).  At K = 14336,
+// N = 4096, 4 bits it takes 8.7 us against 83 us at M = 48, 18.6 against
+// 80 at M = 256, 31.6 against 80.5 at M = 512, 64.8 against 83 at M = 1024; at
+// K = 2048, N = 11008 it stops paying at M = 384 (17.1 against 17.9 us).
 template <int BITS>
 int auto_kernel(int64_t M, int64_t N, int K) {
   if (M <= 16) return kGemmDecode;
   using S = PrefillCfg<BITS>;
   using W = Wide<BITS>;
   const int cus = device_cus();
-  if (wide_fits<BITS>(M, N, K) &&
-      launch_cost(M, N, W::kBM, W::kBN, kWideSpeed, cus) <= launch_cost(M, N, S::kBM, S::kBN, 1.0, cus))
-    return kGemmWide;
-  return kGemmTile;
+  const bool wide = wide_fits<BITS>(M, N, K) && launch_cost(M, N, W::kBM, W::kBN, kWideSpeed, cus) <=
+                                                    launch_cost(M, N, S::kBM, S::kBN, 1.0, cus);
+  if (1.08 * ksplit_cost(M, N, K, BITS) < tile_kernel_us(M, N, K, BITS, wide, cus)) return kGemmKsplit;
+  return wide ? kGemmWide : kGemmTile;
 }
 
 template <int BITS, bool ACC_OUT, bool WA8 = false, bool ZP = false>
@@ -1253,8 +1007,10 @@ hipError_t launch_t(const uint8_t* a, const float* as, int64_t M, int K,
   if (kernel == kGemmAuto) kernel = auto_kernel<BITS>(M, N, K);
   switch (kernel) {
     case kGemmDecode:
-      launch_decode<BITS, ACC_OUT, WA8, ZP>(a, as, M, K, w, ws, N, y, acc, az, wsum, stream);
-      break;
+    case kGemmKsplit:
+      return launch_ksplit(KsplitCall{a, as, M, K, w, ws, N, ACC_OUT ? nullptr : y, ACC_OUT ? acc : nullptr,
+                                      az, wsum},
+                           BITS, WA8 ? kWeightsA8Order : kWeightsCanonical, stream);
     case kGemmWide:
       launch_wide<BITS, ACC_OUT, WA8, ZP>(a, as, M, K, w, ws, N, y, acc, az, wsum, device_cus(), stream);
       break;
@@ -1345,24 +1101,9 @@ hipError_t launch_pack_decode(const uint8_t* w_packed, int64_t N, int K, uint8_t
 hipError_t launch_qlinear_decode_native(const void* codes, const float* a_scales, int64_t M, int K,
                                         int bits, const uint8_t* w_dec, const float* w_scales,
                                         int64_t N, void* y, int32_t* out_acc, hipStream_t stream) {
-  if (M == 0) return hipSuccess;
-  const uint8_t* a = static_cast<const uint8_t*>(codes);
-  __half* yh = static_cast<__half*>(y);
-  if (out_acc) {
-    if (bits == 4)
-      launch_decode<4, true, false, false, true>(a, nullptr, M, K, w_dec, nullptr, N, nullptr,
-                                                 out_acc, nullptr, nullptr, stream);
-    else
-      launch_decode<8, true, false, false, true>(a, nullptr, M, K, w_dec, nullptr, N, nullptr,
-                                                 out_acc, nullptr, nullptr, stream);
-  } else if (bits == 4) {
-    launch_decode<4, false, false, false, true>(a, a_scales, M, K, w_dec, w_scales, N, yh, nullptr,
-                                                nullptr, nullptr, stream);
-  } else {
-    launch_decode<8, false, false, false, true>(a, a_scales, M, K, w_dec, w_scales, N, yh, nullptr,
-                                                nullptr, nullptr, stream);
-  }
-  return hipGetLastError();
+  return launch_ksplit(KsplitCall{static_cast<const uint8_t*>(codes), a_scales, M, K, w_dec, w_scales, N,
+                                  static_cast<__half*>(y), out_acc, nullptr, nullptr},
+                       bits, kWeightsDecode, stream);
 }
 
 hipError_t launch_qlinear_a8(const void* codes, const float* a_scales, int64_t M, int K,

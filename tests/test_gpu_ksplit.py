@@ -1,0 +1,72 @@
+"""GPU parity of the K-split GEMM (small output tiles whose wavefronts split K)
+at the shapes where it can go wrong: each of its tiles, ragged M and N
+(remainders of 16-token and of 16-channel blocks), K that is not a multiple of
+256 (a last stage of 128 k, row starts off the 128-byte lines) and K with
+fewer stages than wavefronts.
+
+Bar: accumulators and fp16 outputs bit for bit against the oracle's exact GEMM
+and pinned epilogue, for canonical weights, the 8-bit activation order and the
+zero-point correction.  All arithmetic up to the epilogue is integer, so there
+is no tolerance.
+"""
+
+import numpy as np
+import pytest
+
+import workloads
+from oracle.range_quant import weight_sums_ref, zero_point_acc_ref
+from paritylib import assert_acc, oracle_acc, oracle_y, safe_w_scales
+
+torch = pytest.importorskip("torch")
+dptq = pytest.importorskip("paper_2606_12487_amd")
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (M, K, N, bits).  One block of 16 tokens: the three decode tiles.
+    (1, 128, 16, 4), (5, 640, 4624, 8), (16, 384, 10256, 4), (9, 2176, 16400, 8),
+    # the tiles of larger batches, as TI x TJ
+    (17, 128, 16, 4), (18, 384, 48, 8),            # 1 x 1
+    (17, 128, 2064, 4), (31, 640, 2064, 8),        # 1 x 2
+    (17, 128, 6160, 4), (47, 896, 4112, 8),        # 2 x 2
+    (33, 640, 6160, 4), (33, 384, 6160, 8),        # 2 x 3
+    (63, 384, 6160, 4), (17, 640, 11024, 8),       # 4 x 2
+    (129, 384, 4112, 4), (129, 384, 4112, 8),      # 4 x 3
+    (300, 128, 3088, 4), (300, 128, 3088, 8),      # 4 x 4
+    (161, 896, 6160, 4), (161, 2432, 6160, 8),     # 4 x 6
+    (97, 384, 11024, 4), (97, 384, 11024, 8),      # 6 x 4
+    (129, 1408, 11024, 8),                         # 6 x 6
+    (161, 896, 8208, 8),                           # 8 x 4
+]
+
+
+def _d(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda:0")
+
+
+def _h(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+@pytest.mark.parametrize("M,K,N,bits", CASES)
+def test_ksplit_matches_oracle(M, K, N, bits):
+    rng = np.random.default_rng([M, K, N, bits])
+    a = workloads.random_code_bytes(rng, M, K, bits)
+    w = workloads.random_weight_bytes(rng, N, K)
+    a_s = workloads.random_scales(rng, M, 1e-3, 1.0)
+    w_s = safe_w_scales(rng, N, K, a_s, bits)
+    ad, wd, asd, wsd = _d(a), _d(w), _d(a_s), _d(w_s)
+    acc = oracle_acc(a, bits, w)
+    what = f"{M}x{K}x{N} A{bits}"
+    assert_acc(_h(dptq.qlinear_acc(ad, bits, wd)), acc, what)
+    y_ref = oracle_y(acc, a_s, w_s).view(np.uint16)
+    assert np.array_equal(_h(dptq.qlinear(ad, asd, bits, wd, wsd)).view(np.uint16), y_ref), what
+    if bits == 8:
+        y = dptq.qlinear_a8(ad, asd, dptq.pack_w4_a8(wd), wsd)
+        assert np.array_equal(_h(y).view(np.uint16), y_ref), what + " 8-bit order"
+    zeros = rng.integers(0, 2 ** bits, size=M).astype(np.int32)
+    sums = weight_sums_ref(w)
+    z_ref = oracle_y(zero_point_acc_ref(acc, zeros, bits, sums), a_s, w_s * np.float32(0.25))
+    y = dptq.qlinear_range(ad, asd, _d(zeros), bits, wd, _d(w_s * np.float32(0.25)), _d(sums.astype(np.int32)))
+    assert np.array_equal(_h(y).view(np.uint16), z_ref.view(np.uint16)), what + " zero points"
