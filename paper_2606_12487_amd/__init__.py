@@ -1,10 +1,11 @@
 """Python binding of libdptq, the MI355X quantized linear layer of DynamicPTQ.
 
-Thin ctypes marshalling over the C ABI declared in ``include/dptq.h``: the
-functions below check tensor dtypes and shapes, allocate outputs with torch
-(device memory and streams only) and call the library on the current HIP
-stream.  Every arithmetic step runs in the library's kernels; there is no
-fallback path, and importing a function whose library is missing raises.
+Thin marshalling over the C ABI declared in ``include/dptq.h``: the functions
+below check tensor dtypes and shapes, allocate outputs with torch (device
+memory and streams only) and call the library on the current HIP stream, the
+per-call ones in a native module, the offline ones through ctypes.  Every
+arithmetic step runs in the library's kernels; there is no fallback path, and
+calling a function whose library is missing raises.
 
     codes, scales = rotate_quant(x_fp16, had_size=4096, bits=4)
     w_packed, w_scales = prepare_weights(w_fp32, had_size=4096)
@@ -12,6 +13,7 @@ fallback path, and importing a function whose library is missing raises.
 """
 
 import ctypes
+import importlib.util
 import os
 
 __all__ = ["DptqError", "lib", "library_path", "rotate_quant", "qlinear", "qlinear_acc",
@@ -27,7 +29,9 @@ __all__ = ["DptqError", "lib", "library_path", "rotate_quant", "qlinear", "qline
 
 _PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 _LIB_NAME = "libdptq.so"
+_BINDING_NAME = "_dptq_torch.so"
 _lib = None
+_native = None
 
 # Every function the C ABI exports (include/dptq.h).
 EXPORTED_FUNCTIONS = ("dptq_status_string", "dptq_version", "dptq_rotate_quant",
@@ -133,6 +137,29 @@ def lib():
     return _lib
 
 
+def _binding():
+    """The native half of the per-call functions (csrc/torch_binding.cpp), on
+    the loaded libdptq."""
+    global _native
+    if _native is None:
+        lib()
+        path = os.path.join(_PKG_DIR, _BINDING_NAME)
+        if not os.path.exists(path):
+            raise RuntimeError(
+                f"{path} is missing: build it with `python -m paper_2606_12487_amd.build` "
+                "(there is no fallback)")
+        torch = _torch()   # its libraries are in the process before the module's
+        spec = importlib.util.spec_from_file_location("_dptq_torch", path)
+        m = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(m)
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is None:
+            raw = lambda i: torch.cuda.current_stream(i).cuda_stream  # noqa: E731
+        m.init(_check, raw)
+        _native = m
+    return _native
+
+
 def _status_string(status):
     try:
         return lib().dptq_status_string(int(status)).decode()
@@ -193,29 +220,7 @@ def _signs_arg(signs, K, dev):
 def rotate_quant(x, had_size, bits, codes=None, scales=None, signs=None):
     """Rotate (I (x) H_h) and quantize fp16 rows x [M, K] -> (codes, fp32 scales [M]).
     signs: optional uint8 bitmask [ceil(K/8)] of randomized signs (bit set = -1)."""
-    torch = _torch()
-    _require(x, "x", torch.float16)
-    if x.dim() != 2:
-        raise ValueError("x must be 2-D [M, K]")
-    M, K = x.shape
-    if bits not in (4, 8):
-        raise ValueError("bits must be 4 or 8")
-    cdt = torch.uint8 if bits == 4 else torch.int8
-    if codes is None:
-        codes = torch.empty(code_shape(M, K, bits), dtype=cdt, device=x.device)
-    _require(codes, "codes", cdt, code_shape(M, K, bits))
-    if scales is None:
-        scales = torch.empty((M,), dtype=torch.float32, device=x.device)
-    _require(scales, "scales", torch.float32, (M,))
-    signs = _signs_arg(signs, K, x.device)
-    if signs is None:
-        _check(lib().dptq_rotate_quant(_ptr(x), M, K, int(had_size), int(bits), _ptr(codes),
-                                       _ptr(scales), _stream(x)), "dptq_rotate_quant")
-    else:
-        _check(lib().dptq_rotate_quant_ex(_ptr(x), M, K, int(had_size), int(bits), _ptr(signs),
-                                          LAYOUT_PACKED, _ptr(codes), _ptr(scales), _stream(x)),
-               "dptq_rotate_quant_ex")
-    return codes, scales
+    return _binding().rotate_quant(x, had_size, bits, codes, scales, signs)
 
 
 def _gemm_args(codes, bits, w_packed):
@@ -236,21 +241,7 @@ def _gemm_args(codes, bits, w_packed):
 def qlinear(codes, a_scales, bits, w_packed, w_scales, y=None, kernel=GEMM_AUTO):
     """y [M, N] fp16 = dequant(codes . w^T) with per-token x per-channel scales.
     kernel: one of the GEMM_* kernels (default: the library's choice)."""
-    torch = _torch()
-    M, K, N = _gemm_args(codes, bits, w_packed)
-    _require(a_scales, "a_scales", torch.float32, (M,))
-    _require(w_scales, "w_scales", torch.float32, (N,))
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=codes.device)
-    _require(y, "y", torch.float16, (M, N))
-    if kernel == GEMM_AUTO:
-        _check(lib().dptq_qlinear(_ptr(codes), _ptr(a_scales), M, K, int(bits), _ptr(w_packed),
-                                  _ptr(w_scales), N, _ptr(y), _stream(codes)), "dptq_qlinear")
-    else:
-        _check(lib().dptq_qlinear_kernel(_ptr(codes), _ptr(a_scales), M, K, int(bits),
-                                         _ptr(w_packed), _ptr(w_scales), N, _ptr(y), None,
-                                         int(kernel), _stream(codes)), "dptq_qlinear_kernel")
-    return y
+    return _binding().qlinear(codes, a_scales, bits, w_packed, w_scales, y, kernel)
 
 
 def qlinear_acc(codes, bits, w_packed, acc=None, kernel=GEMM_AUTO):
@@ -329,18 +320,7 @@ def _decode_native_args(codes, bits, w_dec, N):
 def qlinear_decode_native(codes, a_scales, bits, w_dec, w_scales, y=None):
     """qlinear for M <= 16 tokens on weights from prepack_weights(w, WEIGHTS_DECODE):
     the same y bit for bit.  N is taken from w_scales."""
-    torch = _torch()
-    N = w_scales.shape[0]
-    M, K = _decode_native_args(codes, bits, w_dec, N)
-    _require(a_scales, "a_scales", torch.float32, (M,))
-    _require(w_scales, "w_scales", torch.float32, (N,))
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=codes.device)
-    _require(y, "y", torch.float16, (M, N))
-    _check(lib().dptq_qlinear_decode_native(_ptr(codes), _ptr(a_scales), M, K, int(bits), _ptr(w_dec),
-                                            _ptr(w_scales), N, _ptr(y), None, _stream(codes)),
-           "dptq_qlinear_decode_native")
-    return y
+    return _binding().qlinear_decode_native(codes, a_scales, bits, w_dec, w_scales, y)
 
 
 def qlinear_decode_native_acc(codes, bits, w_dec, N, acc=None):
@@ -359,16 +339,7 @@ def qlinear_decode_native_acc(codes, bits, w_dec, N, acc=None):
 def qlinear_a8(codes, a_scales, w_a8, w_scales, y=None, kernel=GEMM_AUTO):
     """The W4A8 linear (qlinear with bits = 8) against weights from pack_w4_a8:
     the same y bit for bit."""
-    torch = _torch()
-    M, K, N = _gemm_args(codes, 8, w_a8)
-    _require(a_scales, "a_scales", torch.float32, (M,))
-    _require(w_scales, "w_scales", torch.float32, (N,))
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=codes.device)
-    _require(y, "y", torch.float16, (M, N))
-    _check(lib().dptq_qlinear_a8(_ptr(codes), _ptr(a_scales), M, K, _ptr(w_a8), _ptr(w_scales), N,
-                                 _ptr(y), int(kernel), _stream(codes)), "dptq_qlinear_a8")
-    return y
+    return _binding().qlinear_a8(codes, a_scales, w_a8, w_scales, y, kernel)
 
 
 def residual_dynamics(x, dx, had_size, bits=4, eps=1e-8, jr=None, snr=None, means=None):
@@ -376,27 +347,7 @@ def residual_dynamics(x, dx, had_size, bits=4, eps=1e-8, jr=None, snr=None, mean
     and historical SNR (dB) of the updates dx added to the states x (both fp16
     [T, K]), measured through the rotated `bits`-bit quantizer; returns
     (jr float32 [T], snr float32 [T], means float64 [2] = layer JR, layer SNR)."""
-    torch = _torch()
-    _require(x, "x", torch.float16)
-    if x.dim() != 2:
-        raise ValueError("x must be 2-D [T, K]")
-    T, K = x.shape
-    _require(dx, "dx", torch.float16, (T, K))
-    if bits not in (4, 8):
-        raise ValueError("bits must be 4 or 8")
-    if jr is None:
-        jr = torch.empty((T,), dtype=torch.float32, device=x.device)
-    if snr is None:
-        snr = torch.empty((T,), dtype=torch.float32, device=x.device)
-    if means is None:
-        means = torch.empty((2,), dtype=torch.float64, device=x.device)
-    _require(jr, "jr", torch.float32, (T,))
-    _require(snr, "snr", torch.float32, (T,))
-    _require(means, "means", torch.float64, (2,))
-    _check(lib().dptq_residual_dynamics(_ptr(x), _ptr(dx), T, K, int(had_size), int(bits),
-                                        float(eps), _ptr(jr), _ptr(snr), _ptr(means),
-                                        _stream(x)), "dptq_residual_dynamics")
-    return jr, snr, means
+    return _binding().residual_dynamics(x, dx, had_size, bits, eps, jr, snr, means)
 
 
 def select_layers(jr_layers, snr_layers, tau_jr, tau_snr):
@@ -418,45 +369,12 @@ def select_layers(jr_layers, snr_layers, tau_jr, tau_snr):
 def kv_quant(kv, group=128, codes=None, scales=None, mins=None):
     """Group-wise 4-bit quantization of fp16 KV rows kv [T, D] ->
     (codes uint8 [T, D/2], scales float32 [T, D/group], mins float32 [T, D/group])."""
-    torch = _torch()
-    _require(kv, "kv", torch.float16)
-    if kv.dim() != 2:
-        raise ValueError("kv must be 2-D [T, D]")
-    T, D = kv.shape
-    if group <= 0 or D % group:
-        raise ValueError("D must be a multiple of group")
-    G = D // group
-    if codes is None:
-        codes = torch.empty((T, D // 2), dtype=torch.uint8, device=kv.device)
-    if scales is None:
-        scales = torch.empty((T, G), dtype=torch.float32, device=kv.device)
-    if mins is None:
-        mins = torch.empty((T, G), dtype=torch.float32, device=kv.device)
-    _require(codes, "codes", torch.uint8, (T, D // 2))
-    _require(scales, "scales", torch.float32, (T, G))
-    _require(mins, "mins", torch.float32, (T, G))
-    _check(lib().dptq_kv_quant(_ptr(kv), T, D, int(group), _ptr(codes), _ptr(scales), _ptr(mins),
-                               _stream(kv)), "dptq_kv_quant")
-    return codes, scales, mins
+    return _binding().kv_quant(kv, group, codes, scales, mins)
 
 
 def kv_dequant(codes, scales, mins, group=128, out=None):
     """Reconstruct fp16 [T, D] from kv_quant's output."""
-    torch = _torch()
-    _require(codes, "codes", torch.uint8)
-    if codes.dim() != 2:
-        raise ValueError("codes must be 2-D [T, D/2]")
-    T, D = codes.shape[0], 2 * codes.shape[1]
-    if group <= 0 or D % group:
-        raise ValueError("D must be a multiple of group")
-    _require(scales, "scales", torch.float32, (T, D // group))
-    _require(mins, "mins", torch.float32, (T, D // group))
-    if out is None:
-        out = torch.empty((T, D), dtype=torch.float16, device=codes.device)
-    _require(out, "out", torch.float16, (T, D))
-    _check(lib().dptq_kv_dequant(_ptr(codes), _ptr(scales), _ptr(mins), T, D, int(group),
-                                 _ptr(out), _stream(codes)), "dptq_kv_dequant")
-    return out
+    return _binding().kv_dequant(codes, scales, mins, group, out)
 
 
 def layer_policy(num_layers, mask=None):
@@ -528,27 +446,7 @@ def pack_fp6(codes, out=None):
 def rotate_quant_fp6(x, had_size, out=None, scales=None, signs=None):
     """Rotate and quantize fp16 rows x [M, K] at 4 bits, codes written in the
     FP6 block layout -> (uint8 [fp6_bytes(M, K)], fp32 scales [M])."""
-    torch = _torch()
-    _require(x, "x", torch.float16)
-    if x.dim() != 2:
-        raise ValueError("x must be 2-D [M, K]")
-    M, K = x.shape
-    n = fp6_bytes(M, K)
-    if out is None:
-        out = torch.empty((n,), dtype=torch.uint8, device=x.device)
-    _require(out, "out", torch.uint8, (n,))
-    if scales is None:
-        scales = torch.empty((M,), dtype=torch.float32, device=x.device)
-    _require(scales, "scales", torch.float32, (M,))
-    signs = _signs_arg(signs, K, x.device)
-    if signs is None:
-        _check(lib().dptq_rotate_quant_fp6(_ptr(x), M, K, int(had_size), _ptr(out), _ptr(scales),
-                                           _stream(x)), "dptq_rotate_quant_fp6")
-    else:
-        _check(lib().dptq_rotate_quant_ex(_ptr(x), M, K, int(had_size), 4, _ptr(signs), LAYOUT_FP6,
-                                          _ptr(out), _ptr(scales), _stream(x)),
-               "dptq_rotate_quant_ex")
-    return out, scales
+    return _binding().rotate_quant_fp6(x, had_size, out, scales, signs)
 
 
 def _fp6_args(a6, w6, M, K, N):
@@ -560,16 +458,7 @@ def _fp6_args(a6, w6, M, K, N):
 def qlinear_fp6(a6, a_scales, w6, w_scales, M, K, N, y=None):
     """y [M, N] fp16 = dequant(a . w^T) for 4-bit codes in the FP6 block layout
     (the same bits as qlinear at 4 bits)."""
-    torch = _torch()
-    _fp6_args(a6, w6, M, K, N)
-    _require(a_scales, "a_scales", torch.float32, (M,))
-    _require(w_scales, "w_scales", torch.float32, (N,))
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=a6.device)
-    _require(y, "y", torch.float16, (M, N))
-    _check(lib().dptq_qlinear_fp6(_ptr(a6), _ptr(a_scales), M, K, _ptr(w6), _ptr(w_scales), N,
-                                  _ptr(y), None, _stream(a6)), "dptq_qlinear_fp6")
-    return y
+    return _binding().qlinear_fp6(a6, a_scales, w6, w_scales, M, K, N, y)
 
 
 def qlinear_fp6_acc(a6, w6, M, K, N, acc=None):
@@ -591,48 +480,13 @@ def qlinear_decode_fused(x, had_size, bits, w_packed, w_scales, y=None, codes=No
                          scales=None, mode=DECODE_AUTO):
     """Decode-shape (M <= 16) rotate + quantize + GEMM from fp16 x: one launch
     or two (mode, DECODE_AUTO picks).  Returns (y [M, N] fp16, codes, scales)."""
-    torch = _torch()
-    _require(x, "x", torch.float16)
-    M, K = x.shape
-    N = w_packed.shape[0]
-    _require(w_packed, "w_packed", torch.uint8, (N, K // 2))
-    _require(w_scales, "w_scales", torch.float32, (N,))
-    cdt = torch.uint8 if bits == 4 else torch.int8
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=x.device)
-    if codes is None:
-        codes = torch.empty(code_shape(M, K, bits), dtype=cdt, device=x.device)
-    if scales is None:
-        scales = torch.empty((M,), dtype=torch.float32, device=x.device)
-    _require(y, "y", torch.float16, (M, N))
-    _require(codes, "codes", cdt, code_shape(M, K, bits))
-    _require(scales, "scales", torch.float32, (M,))
-    _check(lib().dptq_qlinear_decode_fused(_ptr(x), M, K, int(had_size), int(bits), _ptr(w_packed),
-                                           _ptr(w_scales), N, _ptr(y), _ptr(codes), _ptr(scales),
-                                           int(mode), _stream(x)), "dptq_qlinear_decode_fused")
-    return y, codes, scales
+    return _binding().qlinear_decode_fused(x, had_size, bits, w_packed, w_scales, y, codes, scales, mode)
 
 
 def rotate_quant_range(x, had_size, bits, codes=None, scales=None, zeros=None):
     """Rotation + per-token range quantization with an integer zero point.
     Returns (codes, scales fp32 [M], zeros int32 [M])."""
-    torch = _torch()
-    _require(x, "x", torch.float16)
-    M, K = x.shape
-    cdt = torch.uint8 if bits == 4 else torch.int8
-    if codes is None:
-        codes = torch.empty(code_shape(M, K, bits), dtype=cdt, device=x.device)
-    if scales is None:
-        scales = torch.empty((M,), dtype=torch.float32, device=x.device)
-    if zeros is None:
-        zeros = torch.empty((M,), dtype=torch.int32, device=x.device)
-    _require(codes, "codes", cdt, code_shape(M, K, bits))
-    _require(scales, "scales", torch.float32, (M,))
-    _require(zeros, "zeros", torch.int32, (M,))
-    _check(lib().dptq_rotate_quant_range(_ptr(x), M, K, int(had_size), int(bits), _ptr(codes),
-                                         _ptr(scales), _ptr(zeros), _stream(x)),
-           "dptq_rotate_quant_range")
-    return codes, scales, zeros
+    return _binding().rotate_quant_range(x, had_size, bits, codes, scales, zeros)
 
 
 def weight_sums(w_packed, out=None):
@@ -651,20 +505,4 @@ def weight_sums(w_packed, out=None):
 def qlinear_range(codes, scales, zeros, bits, w_packed, w_scales, w_sums, y=None):
     """Quantized linear on range-quantized activations (zero-point corrected
     in the GEMM epilogue).  Returns y [M, N] fp16."""
-    torch = _torch()
-    M = scales.shape[0]
-    N, K2 = w_packed.shape
-    K = 2 * K2
-    _require(codes, "codes", torch.uint8 if bits == 4 else torch.int8, code_shape(M, K, bits))
-    _require(scales, "scales", torch.float32, (M,))
-    _require(zeros, "zeros", torch.int32, (M,))
-    _require(w_packed, "w_packed", torch.uint8, (N, K2))
-    _require(w_scales, "w_scales", torch.float32, (N,))
-    _require(w_sums, "w_sums", torch.int32, (N,))
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=codes.device)
-    _require(y, "y", torch.float16, (M, N))
-    _check(lib().dptq_qlinear_range(_ptr(codes), _ptr(scales), _ptr(zeros), M, K, int(bits),
-                                    _ptr(w_packed), _ptr(w_scales), _ptr(w_sums), N, _ptr(y),
-                                    _stream(codes)), "dptq_qlinear_range")
-    return y
+    return _binding().qlinear_range(codes, scales, zeros, bits, w_packed, w_scales, w_sums, y)

@@ -1,4 +1,5 @@
-"""Build libdptq.so (gfx950) in-tree with hipcc.
+"""Build libdptq.so (gfx950) in-tree with hipcc, and the native half of the
+Python binding (_dptq_torch.so, host code) with g++.
 
     python -m paper_2606_12487_amd.build          # build, print the path
 
@@ -7,10 +8,12 @@ tree.  Every HIP source is compiled with IEEE fp32 semantics (no fast-math, no
 contraction) because the kernels reproduce a pinned rounding sequence.
 """
 
+import importlib.util
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG_DIR)
@@ -18,6 +21,8 @@ CSRC = os.path.join(PKG_DIR, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(PKG_DIR, "_build")
 LIB_PATH = os.path.join(PKG_DIR, "libdptq.so")
+BINDING_SOURCE = os.path.join(CSRC, "torch_binding.cpp")
+BINDING_PATH = os.path.join(PKG_DIR, "_dptq_torch.so")
 
 SOURCES = ["rotate_quant.hip", "decode_fused.hip", "qgemm_ksplit.hip", "range_quant.hip", "qgemm.hip", "qgemm_fp6.hip",
            "kv_quant.hip", "dptq_api.hip"]
@@ -50,8 +55,19 @@ def _run(cmd, verbose):
         print(out, flush=True)
 
 
+def _binding_cmd(out):
+    """The g++ command of the binding module, against torch's headers."""
+    torch_dir = list(importlib.util.find_spec("torch").submodule_search_locations)[0]
+    return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+            f"-I{torch_dir}/include", f"-I{torch_dir}/include/torch/csrc/api/include",
+            f"-I{sysconfig.get_paths()['include']}", f"-I{INCLUDE}", BINDING_SOURCE, "-o", out,
+            f"-L{torch_dir}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", f"-L{PKG_DIR}", "-ldptq",
+            "-Wl,-rpath,$ORIGIN"]
+
+
 def build(verbose=False, jobs=8):
-    """Compile every source and link libdptq.so; returns the library path."""
+    """Compile every source, link libdptq.so and the binding module; returns the
+    library path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     hipcc = _hipcc()
     objs = []
@@ -76,6 +92,9 @@ def build(verbose=False, jobs=8):
     tmp = LIB_PATH + ".tmp"
     _run([hipcc, f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp], verbose)
     os.replace(tmp, LIB_PATH)
+    tmp = BINDING_PATH + ".tmp"
+    _run(_binding_cmd(tmp), verbose)
+    os.replace(tmp, BINDING_PATH)
     return LIB_PATH
 
 

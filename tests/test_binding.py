@@ -1,0 +1,52 @@
+"""The argument checks of the Python binding's per-call functions: what they
+refuse, with which error, and that buffers passed in are the ones returned."""
+
+import pytest
+
+torch = pytest.importorskip("torch")
+dptq = pytest.importorskip("paper_2606_12487_amd")
+
+
+@pytest.mark.parametrize("call,error,text", [
+    (lambda: dptq.rotate_quant(1, 8, 4), TypeError, "x must be a torch.Tensor"),
+    (lambda: dptq.rotate_quant(torch.zeros(2, 8), 8, 4), TypeError,
+     "x must have dtype torch.float16, got torch.float32"),
+    (lambda: dptq.kv_quant(torch.zeros(2, 8).half()), ValueError, "kv must be a GPU tensor"),
+    (lambda: dptq.qlinear(torch.zeros(2, 8), None, 5, None, None), ValueError, "bits must be 4 or 8"),
+    (lambda: dptq.qlinear(torch.zeros(2, 8), None, 4.5, None, None), ValueError, "bits must be 4 or 8"),
+    (lambda: dptq.qlinear_fp6(None, None, None, None, 3, 100, 16), ValueError,
+     "no FP6 layout for rows=3, K=100"),
+])
+def test_refusals(call, error, text):
+    dptq.lib()
+    with pytest.raises(error, match=text.replace("(", r"\(")):
+        call()
+
+
+@pytest.mark.gpu
+def test_buffers_shapes_and_statuses():
+    x = torch.randn(3, 256, device="cuda").half()
+    codes = torch.empty((3, 128), dtype=torch.uint8, device="cuda")
+    scales = torch.empty((3,), device="cuda")
+    c, s = dptq.rotate_quant(x, 256, 4, codes, scales)
+    assert c is codes and s is scales
+    c2, s2 = dptq.rotate_quant(x, had_size=256, bits=4)
+    assert torch.equal(c2, codes) and torch.equal(s2, scales)
+    with pytest.raises(ValueError, match=r"codes must have shape \(3, 256\), got \(3, 128\)"):
+        dptq.rotate_quant(x, 256, 8, codes.view(torch.int8))
+    with pytest.raises(ValueError, match=r"scales must have shape \(3,\), got \(4,\)"):
+        dptq.rotate_quant(x, 256, 4, codes, torch.empty((4,), device="cuda"))
+    with pytest.raises(ValueError, match="x must be contiguous"):
+        dptq.rotate_quant(torch.randn(256, 3, device="cuda").half().t(), 256, 4)
+    with pytest.raises(ValueError, match="x must be 2-D"):
+        dptq.rotate_quant(x[0], 256, 4)
+    with pytest.raises(dptq.DptqError) as e:
+        dptq.rotate_quant(x, 100, 4)
+    assert e.value.status == 1
+    # a side stream's work is ordered by that stream
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        c3, s3 = dptq.rotate_quant(x, 256, 4)
+    side.synchronize()
+    assert torch.equal(c3, codes) and torch.equal(s3, scales)
