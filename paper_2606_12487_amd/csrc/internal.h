@@ -152,5 +152,16 @@ hipError_t launch_pack_fp6(const uint8_t* codes, int64_t R, int K, uint8_t* out,
 hipError_t launch_qlinear_fp6(const uint8_t* a6, const float* a_scales, int64_t M, int K,
                               const uint8_t* w6, const float* w_scales, int64_t N, void* y,
                               int32_t* out_acc, hipStream_t stream);
+// Its kernel for medium batches (qgemm_fp6_ksplit.hip): the best tile and its
+// estimated microseconds (tile -1: none in the range of the estimates, unless
+// any_size), and one launch of it.
+struct Fp6KsplitPlan {
+  int tile;
+  double cost;
+};
+Fp6KsplitPlan fp6_ksplit_plan(int64_t M, int64_t N, int K, bool any_size);
+hipError_t launch_fp6_ksplit(int tile, const uint8_t* a6, const float* a_scales, int64_t M, int K,
+                             const uint8_t* w6, const float* w_scales, int64_t N, void* y, int32_t* acc,
+                             hipStream_t stream);
 
 }  // namespace dptq

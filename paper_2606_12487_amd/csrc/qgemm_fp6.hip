@@ -27,6 +27,7 @@
 // LDS into six consecutive registers as three 8-byte reads per lane, free of
 // bank conflicts.
 
+#include "fp6_device.h"
 #include "internal.h"
 
 #include <utility>
@@ -34,11 +35,7 @@
 namespace dptq {
 namespace {
 
-typedef int v8i_t __attribute__((ext_vector_type(8)));
-typedef float v16f_t __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) uint8_t* lds_ptr_t;
-
-constexpr int kF6Block = 3072;   // bytes of one 32-row x 128-k block
+using namespace f6;
 
 // e2m3 encoding of c / 2 for the 4-bit two's complement nibble n (c = n for
 // n < 8, n - 16 otherwise): byte n & 3 of one of four dwords (c = 0..3, 4..7,
@@ -123,12 +120,6 @@ struct F6 {
   static constexpr int nl(int w) { return w < 2 ? 11 : 10; }
 };
 
-__device__ __forceinline__ void f6_dma16(const void* sbase, uint32_t voff, uint32_t lds_off) {
-  asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
-               :
-               : "v"(voff), "s"(sbase), "s"(lds_off)
-               : "memory", "m0");
-}
 // The same with the LDS destination a wavefront-uniform base plus a
 // compile-time offset, formed in M0 by one scalar add; the global address is
 // sbase + voff.
@@ -154,12 +145,6 @@ __device__ __forceinline__ void f6_wait_vmcnt() {
 }
 __device__ __forceinline__ void f6_wait_lgkm0() {
   __builtin_amdgcn_s_waitcnt((15) | (3 << 14) | (7 << 4) | (0 << 8));
-}
-
-__device__ __forceinline__ int f6_xcd_remap(int bid, int total) {
-  const int per = total >> 3, rem = total & 7;
-  const int x = bid & 7, idx = bid >> 3;
-  return x * per + (x < rem ? x : rem) + idx;
 }
 
 // Scheduling groups: NM MFMAs, each followed by two LDS reads for the first
@@ -193,37 +178,10 @@ constexpr int f6_part_after(int f, int frags, int parts) {
   return 0;
 }
 
-// One MFMA step: fp6 x fp6, E8M0 scale 128 (= 2) on both operands.
-__device__ __forceinline__ v16f_t mfma_f6(const uint32_t* w, const uint32_t* a, v16f_t c) {
-  const v8i_t wa = {(int)w[0], (int)w[1], (int)w[2], (int)w[3], (int)w[4], (int)w[5], 0, 0};
-  const v8i_t ab = {(int)a[0], (int)a[1], (int)a[2], (int)a[3], (int)a[4], (int)a[5], 0, 0};
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wa, ab, c, 2, 2, 0, 128, 0, 128);
-}
-
-// fl16(fl32(fl32(acc) * as) * ws); acc is an exact integer held in fp32.  The
-// empty asm keeps the second product an fp32 value (see the int8 kernels).
-__device__ __forceinline__ __half f6_dequant(float acc, float as, float ws) {
-  const float t1 = acc * as;
-  float t2 = t1 * ws;
-  asm("" : "+v"(t2));
-  return __float2half_rn(t2);
-}
-
-__device__ __forceinline__ uint2 f6_dequant4(float a0, float a1, float a2, float a3, float as,
-                                             float4 ws) {
-  const __half h0 = f6_dequant(a0, as, ws.x), h1 = f6_dequant(a1, as, ws.y);
-  const __half h2 = f6_dequant(a2, as, ws.z), h3 = f6_dequant(a3, as, ws.w);
-  uint2 pk;
-  pk.x = (uint32_t)__half_as_ushort(h0) | ((uint32_t)__half_as_ushort(h1) << 16);
-  pk.y = (uint32_t)__half_as_ushort(h2) | ((uint32_t)__half_as_ushort(h3) << 16);
-  return pk;
-}
-
-// Body of the GEMM for wavefront WV of a workgroup.  Fast shapes (at least
-// one full tile of padded rows each way and three stages per tile) shift edge
-// tiles inward so every load is a base plus a constant; the CLAMP variant
-// (small shapes) clamps each block row instead.
-template <int WV, bool ACC_OUT, bool CLAMP>
+// Body of the GEMM for wavefront WV of a workgroup.  Shapes have at least one
+// full tile of padded rows each way and three stages per tile; edge tiles are
+// shifted inward so every load is a base plus a constant.
+template <int WV, bool ACC_OUT>
 __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
                                                const float* __restrict__ a_scales,
                                                const uint8_t* __restrict__ w6,
@@ -259,10 +217,8 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
     const int tn = t / gm, tm = g * kGroupM + (t - tn * gm);
     m0 = tm * C::kBM;
     n0 = tn * C::kBN;
-    if constexpr (!CLAMP) {
-      m0 = min(m0, mblk * 32 - C::kBM);
-      n0 = min(n0, nblk * 32 - C::kBN);
-    }
+    m0 = min(m0, mblk * 32 - C::kBM);
+    n0 = min(n0, nblk * 32 - C::kBN);
   };
 
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
@@ -273,42 +229,26 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
   // into ring buffer buf.  Load q < 18 is part q % 3 of weight block q / 3,
   // load q >= 18 part of activation block (q - 18) / 3; it lands at q KiB.
   // Loads P0 .. P1 - 1 of this wavefront's NL.
-  auto issue_part = [&](const uint8_t* wt, const uint8_t* at, int rbw, int rba, int kb, int buf, auto p0c,
-                        auto p1c) __attribute__((always_inline)) {
+  auto issue_part = [&](const uint8_t* wt, const uint8_t* at, int kb, int buf, auto p0c, auto p1c) __attribute__((always_inline)) {
     constexpr int P0 = decltype(p0c)::value, P1 = decltype(p1c)::value;
     const uint8_t* wst = wt + (size_t)kb * wstride;
     const uint8_t* ast = at + (size_t)kb * astride;
     const uint32_t base = smem_base + buf * C::kStage;
-    if constexpr (!CLAMP) {
-      // Contiguous: load q reads 1 KiB at a constant offset from the stage base.
-      auto one = [&](auto qc) __attribute__((always_inline)) {
-        constexpr int q = decltype(qc)::value;
-        constexpr int rel = q < C::kWLoads ? q : q - C::kWLoads;
-        // The block offset travels in the per-lane offset (one vector
-        // instruction) and the LDS offset in M0's add, so a load costs one
-        // scalar instruction beside it.
-        f6_dma16_at<(uint32_t)(q * 1024)>(q < C::kWLoads ? wst : ast, lane16 + (uint32_t)(rel * 1024), base);
-      };
-      [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
-        (one(std::integral_constant<int, Q0 + P0 + I>{}), ...);
-      }(std::make_integer_sequence<int, P1 - P0>{});
-    } else {
-#pragma unroll
-      for (int i = P0; i < P1; ++i) {
-        const int q = Q0 + i;
-        const bool isa = q >= C::kWLoads;
-        const int qq = isa ? q - C::kWLoads : q;
-        const int b = qq / 3;
-        const int rb = isa ? min(rba + b, mblk - 1) : min(rbw + b, nblk - 1);
-        const uint8_t* src = (isa ? a6 + (size_t)kb * astride : w6 + (size_t)kb * wstride) +
-                             (uint32_t)(rb * kF6Block + (qq - 3 * b) * 1024);
-        f6_dma16(src, lane16, base + q * 1024);
-      }
-    }
+    // Contiguous: load q reads 1 KiB at a constant offset from the stage base.
+    auto one = [&](auto qc) __attribute__((always_inline)) {
+      constexpr int q = decltype(qc)::value;
+      constexpr int rel = q < C::kWLoads ? q : q - C::kWLoads;
+      // The block offset travels in the per-lane offset (one vector
+      // instruction) and the LDS offset in M0's add, so a load costs one
+      // scalar instruction beside it.
+      f6_dma16_at<(uint32_t)(q * 1024)>(q < C::kWLoads ? wst : ast, lane16 + (uint32_t)(rel * 1024), base);
+    };
+    [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+      (one(std::integral_constant<int, Q0 + P0 + I>{}), ...);
+    }(std::make_integer_sequence<int, P1 - P0>{});
   };
-  auto issue = [&](const uint8_t* wt, const uint8_t* at, int rbw, int rba, int kb, int buf)
-      __attribute__((always_inline)) {
-    issue_part(wt, at, rbw, rba, kb, buf, std::integral_constant<int, 0>{}, std::integral_constant<int, NL>{});
+  auto issue = [&](const uint8_t* wt, const uint8_t* at, int kb, int buf) __attribute__((always_inline)) {
+    issue_part(wt, at, kb, buf, std::integral_constant<int, 0>{}, std::integral_constant<int, NL>{});
   };
   // Scales of tile r into slot r & 1 (only when producing y): wavefront 0
   // loads a_s [256], wavefront 1 w_s [192], 4 bytes per lane, rows clamped.
@@ -365,8 +305,7 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
   // this stage's buffer and the next stage is read into nxt, all between
   // this stage's 24 MFMAs.  The scheduling fences keep that order.
   constexpr int kParts = 5;   // parts a stage's loads are issued in
-  auto stage = [&](const Frag& cur, Frag& nxt, int buf, const uint8_t* wt, const uint8_t* at,
-                   int rbw, int rba, int kbi) __attribute__((always_inline)) {
+  auto stage = [&](const Frag& cur, Frag& nxt, int buf, const uint8_t* wt, const uint8_t* at, int kbi) __attribute__((always_inline)) {
     const int nbuf = buf == 2 ? 0 : buf + 1;
     f6_wait_lgkm0();
     f6_wait_vmcnt<NL>();
@@ -378,7 +317,7 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
     // [k NL / kParts, (k + 1) NL / kParts) and follows read k * kFrags / kParts - 1.
     constexpr int kFrags = 2 * (kTI + kTJ);
     const uint8_t* s = smem + nbuf * C::kStage;
-    issue_part(wt, at, rbw, rba, kbi, buf, std::integral_constant<int, 0>{},
+    issue_part(wt, at, kbi, buf, std::integral_constant<int, 0>{},
                std::integral_constant<int, NL / kParts>{});
     [&]<int... F>(std::integer_sequence<int, F...>) __attribute__((always_inline)) {
       (
@@ -390,7 +329,7 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
               read_frag(s + st * 1536 + kAOff + (x - kTI) * kF6Block, nxt.a[st][x - kTI]);
             constexpr int k = f6_part_after(F, kFrags, kParts);
             if constexpr (k > 0)
-              issue_part(wt, at, rbw, rba, kbi, buf, std::integral_constant<int, k * NL / kParts>{},
+              issue_part(wt, at, kbi, buf, std::integral_constant<int, k * NL / kParts>{},
                          std::integral_constant<int, (k + 1) * NL / kParts>{});
           }(),
           ...);
@@ -460,38 +399,27 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
     }
   };
 
-  // Issue targets.  In the fast shapes a stage issued three ahead is in the
-  // current tile or the next (a tile has at least three stages); past the
-  // workgroup's last stage the last stage is issued again into a buffer
-  // nobody reads any more, so every stage issues the same loads.  The CLAMP
-  // variant looks up any tile up to three ahead.
+  // Issue targets.  A stage issued three ahead is in the current tile or the
+  // next (a tile has at least three stages); past the workgroup's last stage
+  // the last stage is issued again into a buffer nobody reads any more, so
+  // every stage issues the same loads.
   struct Tgt {
     const uint8_t* wt;
     const uint8_t* at;
-    int rbw, rba, kb;
+    int kb;
   };
   auto tile_base = [&](int r, Tgt& tg) __attribute__((always_inline)) {
     int m0, n0;
     origin(r, m0, n0);
-    tg.rbw = n0 / 32;
-    tg.rba = m0 / 32;
-    tg.wt = w6 + (size_t)tg.rbw * kF6Block;
-    tg.at = a6 + (size_t)tg.rba * kF6Block;
+    tg.wt = w6 + (size_t)(n0 / 32) * kF6Block;
+    tg.at = a6 + (size_t)(m0 / 32) * kF6Block;
   };
   auto target = [&](int r, int kb, const Tgt& cur_t, const Tgt& next_t) __attribute__((always_inline)) {
-    Tgt tg;
     const int k3 = kb + 3;
-    if constexpr (!CLAMP) {
-      const bool in_next = k3 >= nkb;
-      const bool has_next = r + 1 < ntile;
-      tg = (in_next && has_next) ? next_t : cur_t;
-      tg.kb = in_next ? (has_next ? k3 - nkb : nkb - 1) : k3;
-    } else {
-      const int w = (k3 >= nkb) + (k3 >= 2 * nkb) + (k3 >= 3 * nkb);
-      const bool past = r + w >= ntile;
-      tile_base(past ? ntile - 1 : r + w, tg);
-      tg.kb = past ? nkb - 1 : k3 - w * nkb;
-    }
+    const bool in_next = k3 >= nkb;
+    const bool has_next = r + 1 < ntile;
+    Tgt tg = (in_next && has_next) ? next_t : cur_t;
+    tg.kb = in_next ? (has_next ? k3 - nkb : nkb - 1) : k3;
     return tg;
   };
 
@@ -503,7 +431,7 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const Tgt tg = target(0, i - 3, t_cur, t_next);
-    issue(tg.wt, tg.at, tg.rbw, tg.rba, tg.kb, i);
+    issue(tg.wt, tg.at, tg.kb, i);
   }
   // Stage 0 has landed once only stages 1 and 2 are outstanding.
   f6_wait_vmcnt<2 * NL>();
@@ -528,15 +456,15 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
     int kb = 0;
     for (; kb + 1 < nkb; kb += 2) {
       Tgt tg = target(r, kb, t_cur, t_next);
-      stage(fa, fb, buf, tg.wt, tg.at, tg.rbw, tg.rba, tg.kb);
+      stage(fa, fb, buf, tg.wt, tg.at, tg.kb);
       buf = buf == 2 ? 0 : buf + 1;
       tg = target(r, kb + 1, t_cur, t_next);
-      stage(fb, fa, buf, tg.wt, tg.at, tg.rbw, tg.rba, tg.kb);
+      stage(fb, fa, buf, tg.wt, tg.at, tg.kb);
       buf = buf == 2 ? 0 : buf + 1;
     }
     if (kb < nkb) {
       const Tgt tg = target(r, kb, t_cur, t_next);
-      stage(fa, fb, buf, tg.wt, tg.at, tg.rbw, tg.rba, tg.kb);
+      stage(fa, fb, buf, tg.wt, tg.at, tg.kb);
       buf = buf == 2 ? 0 : buf + 1;
       fa = fb;
     }
@@ -552,17 +480,17 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
   f6_wait_vmcnt<0>();   // the re-issued tail loads land before the LDS is released
 }
 
-template <bool ACC_OUT, bool CLAMP>
+template <bool ACC_OUT>
 __global__ void __launch_bounds__(256)
 qgemm_fp6(const uint8_t* __restrict__ a6, const float* __restrict__ a_scales,
           const uint8_t* __restrict__ w6, const float* __restrict__ w_scales, int M, int N,
           int K, __half* __restrict__ y, int32_t* __restrict__ acc_out) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[F6::kLds];
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: qgemm_fp6_body<0, ACC_OUT, CLAMP>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
-    case 1: qgemm_fp6_body<1, ACC_OUT, CLAMP>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
-    case 2: qgemm_fp6_body<2, ACC_OUT, CLAMP>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
-    default: qgemm_fp6_body<3, ACC_OUT, CLAMP>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
+    case 0: qgemm_fp6_body<0, ACC_OUT>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
+    case 1: qgemm_fp6_body<1, ACC_OUT>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
+    case 2: qgemm_fp6_body<2, ACC_OUT>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
+    default: qgemm_fp6_body<3, ACC_OUT>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
   }
 }
 
@@ -583,28 +511,26 @@ hipError_t launch_qlinear_fp6(const uint8_t* a6, const float* a_scales, int64_t 
                               const uint8_t* w6, const float* w_scales, int64_t N, void* y,
                               int32_t* out_acc, hipStream_t stream) {
   if (M == 0) return hipSuccess;
+  // This kernel takes at least one full tile of padded rows each way and
+  // three stages per tile; of those shapes it runs the ones whose estimated
+  // microseconds are not above the K-split kernel's by 5% or more (whole rounds of
+  // 192 x 256 tiles, 6.9 us + 4.0 ns per k each, and the operands' and the
+  // output's way; fitted like the K-split kernel's tiles).
   const int64_t tiles = ((M + F6::kBM - 1) / F6::kBM) * ((N + F6::kBN - 1) / F6::kBN);
-  const int cus = device_cus();
-  const int64_t grid = tiles < cus ? tiles : cus;
-  // Fast shapes: at least one full tile of padded rows each way and three
-  // stages per tile.
-  const bool clamp = (M + 31) / 32 < F6::kABlk || (N + 31) / 32 < F6::kWBlk || K < 3 * 128;
+  const int64_t cus = device_cus(), grid = tiles < cus ? tiles : cus;
+  const bool fits = (M + 31) / 32 >= F6::kABlk && (N + 31) / 32 >= F6::kWBlk && K >= 3 * 128;
+  const double rounds = (double)((tiles + cus - 1) / cus), k = (double)K, n = (double)N;
+  const double cost = rounds * (6.91 + 3.99e-3 * k) + 5.98e-8 * k * n + 1.84e-7 * (double)M * n;
+  const Fp6KsplitPlan plan = fp6_ksplit_plan(M, N, K, !fits);
+  if (plan.tile >= 0 && (!fits || plan.cost < 0.95 * cost))
+    return launch_fp6_ksplit(plan.tile, a6, a_scales, M, K, w6, w_scales, N, y, out_acc, stream);
   __half* yh = static_cast<__half*>(y);
-  if (out_acc) {
-    if (clamp)
-      hipLaunchKernelGGL((qgemm_fp6<true, true>), dim3((unsigned)grid), dim3(256), 0, stream, a6,
-                         a_scales, w6, w_scales, (int)M, (int)N, K, yh, out_acc);
-    else
-      hipLaunchKernelGGL((qgemm_fp6<true, false>), dim3((unsigned)grid), dim3(256), 0, stream, a6,
-                         a_scales, w6, w_scales, (int)M, (int)N, K, yh, out_acc);
-  } else {
-    if (clamp)
-      hipLaunchKernelGGL((qgemm_fp6<false, true>), dim3((unsigned)grid), dim3(256), 0, stream, a6,
-                         a_scales, w6, w_scales, (int)M, (int)N, K, yh, out_acc);
-    else
-      hipLaunchKernelGGL((qgemm_fp6<false, false>), dim3((unsigned)grid), dim3(256), 0, stream, a6,
-                         a_scales, w6, w_scales, (int)M, (int)N, K, yh, out_acc);
-  }
+  if (out_acc)
+    hipLaunchKernelGGL((qgemm_fp6<true>), dim3((unsigned)grid), dim3(256), 0, stream, a6, a_scales, w6,
+                       w_scales, (int)M, (int)N, K, yh, out_acc);
+  else
+    hipLaunchKernelGGL((qgemm_fp6<false>), dim3((unsigned)grid), dim3(256), 0, stream, a6, a_scales, w6,
+                       w_scales, (int)M, (int)N, K, yh, out_acc);
   return hipGetLastError();
 }
 
