@@ -20,6 +20,8 @@
 // 27.5 us, 17.0 us and 13.8 us for the three, against 75 us for the 256 x 128
 // tile kernel on its 16 workgroups.
 
+#include <math.h>
+
 #include <type_traits>
 
 #include "internal.h"
@@ -41,7 +43,11 @@ __device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t
                : "memory", "m0");
 }
 // Waits that no memory access moves across.
-__device__ __forceinline__ void wait_vmcnt0_fence() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+template <int N>
+__device__ __forceinline__ void wait_vmcnt_fence() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  asm volatile("s_waitcnt vmcnt(%0)" : : "i"(N) : "memory");
+}
 __device__ __forceinline__ void wait_lgkm0_fence() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
 // 16-byte-piece swizzles of 128-byte LDS rows r = 0..15: physical piece p
@@ -57,10 +63,9 @@ __device__ __forceinline__ int swz_byte(int r) { return 2 * ((-(r >> 2)) & 3) + 
 // quantizer's zero-point correction acc + (2^(BITS-1) - a_zeros[m]) * w_sums[n].
 //
 // A wavefront has one stage (256 k) in flight: 16 KiB for 4 x 4 blocks at 4
-// bits, so the eight or more wavefronts of a compute unit keep 64 to 144 KiB
-// on the way, as much as its LDS holds; two or more smaller stages each were
-// no faster (M = 20, K = 14336, N = 4096 at 4 bits: 7.0 us with one, 7.8 us
-// with two).
+// bits, so a compute unit keeps 64 to 160 KiB on the way, as much as its LDS
+// holds; two or more smaller stages each were no faster (M = 20, K = 14336,
+// N = 4096 at 4 bits: 7.0 us with one, 7.8 us with two).
 template <int BITS, int TI, int TJ, int WAVES, bool ACC_OUT, bool WA8, bool ZP, bool WDEC>
 __global__ void __launch_bounds__(WAVES * 64)
 qgemm_ksplit(const uint8_t* __restrict__ a_codes, const float* __restrict__ a_scales,
@@ -70,10 +75,20 @@ qgemm_ksplit(const uint8_t* __restrict__ a_codes, const float* __restrict__ a_sc
   constexpr int kAB = BITS == 4 ? 2 : 4;         // KiB of an activation block per stage
   constexpr int kLoads = 2 * TI + kAB * TJ;      // 1 KiB each, per stage
   constexpr int kStage = kLoads * 1024;
-  constexpr int kRing = WAVES * kStage, kPart = WAVES * WAVES * 1024;
-  constexpr int kFrags = TI * TJ;
+  constexpr int kRing = WAVES * kStage;
+  constexpr int kFrags = TI * TJ, kFragPart = WAVES * 1024;   // one block's partial tiles
+  constexpr int kPart = (kFrags < WAVES ? kFrags : WAVES) * kFragPart;
+  constexpr int kLds = kRing > kPart ? kRing : kPart;
+  constexpr int kPass = kLds / kFragPart < kFrags ? kLds / kFragPart : kFrags;   // blocks summed at a time
   static_assert(kRing <= 160 * 1024, "LDS budget");
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[kRing > kPart ? kRing : kPart];
+  // Refill the stage part by part (below) where there are MFMAs enough to read
+  // under, but not if the second set of fragments costs a resident workgroup:
+  // 4 x 4 blocks at 4 bits, two workgroups a compute unit with 256 registers
+  // each.  M = 333, K = 14336, N = 4096 at 8 bits (4 x 6 blocks): 31.6 us
+  // refilled at once, 26.1 us part by part; M = 512, K = N = 4096 at 4 bits
+  // (4 x 4): 13.3 against 15 us; two to six blocks: the same within 1%.
+  constexpr bool kStream = WAVES == 4 && kFrags >= 8 && (kRing > 80 * 1024 || kFrags < 16);
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[kLds];
   v4i (*part)[WAVES][64] = reinterpret_cast<v4i (*)[WAVES][64]>(smem);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -122,10 +137,9 @@ qgemm_ksplit(const uint8_t* __restrict__ a_codes, const float* __restrict__ a_sc
   // Stage s: blocks of 16 weight rows, then of 16 activation
   // rows (8 bits: its two 128-k halves).  TAIL: the stage without a second
   // half reads its first half twice (the copy is never used).
-  auto load_stage = [&](auto tail, int s) __attribute__((always_inline)) {
+  auto load_w = [&](auto tail, int s) __attribute__((always_inline)) {
     constexpr bool TAIL = decltype(tail)::value;
     const uint8_t* wc = wt + (size_t)s * (WDEC ? 2048 : 128);
-    const uint8_t* ac = at + (size_t)s * (64 * kAB);
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -133,43 +147,55 @@ qgemm_ksplit(const uint8_t* __restrict__ a_codes, const float* __restrict__ a_sc
         const uint32_t o = !TAIL ? wofs[2 * i + q] : WDEC ? wofs[2 * i] : wofs[2 * i + q] - hi[q];
         dma16(wc, o, base + (2 * i + q) * 1024);
       }
+  };
+  auto load_a = [&](auto tail, int s, int j) __attribute__((always_inline)) {
+    constexpr bool TAIL = decltype(tail)::value;
+    const uint8_t* ac = at + (size_t)s * (64 * kAB);
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        const uint32_t la = base + (2 * TI + kAB * j + q) * 1024;
-        if constexpr (BITS == 4) {
-          dma16(ac, TAIL ? aofs[2 * j + q] - hi[q] : aofs[2 * j + q], la);
-        } else {
-          dma16(ac, aofs[2 * j + q], la);
-          dma16(TAIL ? ac : ac + 128, aofs[2 * j + q], la + 2048);
-        }
+    for (int q = 0; q < 2; ++q) {
+      const uint32_t la = base + (2 * TI + kAB * j + q) * 1024;
+      if constexpr (BITS == 4) {
+        dma16(ac, TAIL ? aofs[2 * j + q] - hi[q] : aofs[2 * j + q], la);
+      } else {
+        dma16(ac, aofs[2 * j + q], la);
+        dma16(TAIL ? ac : ac + 128, aofs[2 * j + q], la + 2048);
       }
     }
   };
-  auto load = [&](int s) __attribute__((always_inline)) {
-    if (s < min(s_end, half_stage)) load_stage(std::false_type{}, s);
-    else if (s < s_end) load_stage(std::true_type{}, s);
+  auto part_w = [&](int s) __attribute__((always_inline)) {
+    if (s < half_stage) load_w(std::false_type{}, s);
+    else load_w(std::true_type{}, s);
+  };
+  auto part_a = [&](int s, int j) __attribute__((always_inline)) {
+    if (s < half_stage) load_a(std::false_type{}, s, j);
+    else load_a(std::true_type{}, s, j);
   };
   // Fragments of half h (128 k): lane l has row l & 15 of a block.
-  struct Half {
-    uint4 w[TI];
-    uint4 a[TJ * (BITS == 4 ? 1 : 2)];
+  struct WFrag {
+    uint4 v[2][TI];
   };
-  auto read = [&](int h, Half& b) __attribute__((always_inline)) {
-    const uint32_t rn = (uint32_t)(fr * 128 + ((4 * h + fg) ^ swz_nib(fr)) * 16);
+  struct AFrag {
+    uint4 v[2][BITS == 4 ? 1 : 2];
+  };
+  auto read_w = [&](WFrag& b) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < TI; ++i) b.w[i] = *reinterpret_cast<const uint4*>(stage + i * 2048 + (WDEC ? h * 1024 + lane * 16 : rn));
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int j = 0; j < TJ; ++j) {
-      const uint8_t* sa = stage + (2 * TI + kAB * j) * 1024;
+      for (int i = 0; i < TI; ++i)
+        b.v[h][i] = *reinterpret_cast<const uint4*>(
+            stage + i * 2048 + (WDEC ? h * 1024 + lane * 16 : fr * 128 + ((4 * h + fg) ^ swz_nib(fr)) * 16));
+  };
+  auto read_a = [&](int j, AFrag& b) __attribute__((always_inline)) {
+    const uint8_t* sa = stage + (2 * TI + kAB * j) * 1024;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
       if constexpr (BITS == 4) {
-        b.a[j] = *reinterpret_cast<const uint4*>(sa + rn);
+        b.v[h][0] = *reinterpret_cast<const uint4*>(sa + fr * 128 + ((4 * h + fg) ^ swz_nib(fr)) * 16);
       } else {
 #pragma unroll
         for (int q = 0; q < 2; ++q)
-          b.a[2 * j + q] = *reinterpret_cast<const uint4*>(sa + h * 2048 + fr * 128 +
-                                                           ((2 * fg + q) ^ swz_byte(fr)) * 16);
+          b.v[h][q] = *reinterpret_cast<const uint4*>(sa + h * 2048 + fr * 128 +
+                                                      ((2 * fg + q) ^ swz_byte(fr)) * 16);
       }
     }
   };
@@ -178,72 +204,178 @@ qgemm_ksplit(const uint8_t* __restrict__ a_codes, const float* __restrict__ a_sc
   for (int i = 0; i < TI; ++i)
 #pragma unroll
     for (int j = 0; j < TJ; ++j) acc[i][j] = v4i{0, 0, 0, 0};
-  auto compute = [&](const Half& b) __attribute__((always_inline)) {
+  // Column j of the tile over half h.
+  auto compute = [&](const WFrag& w, const AFrag& a, int j, int h) __attribute__((always_inline)) {
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      v4i aop[TJ];
-#pragma unroll
-      for (int j = 0; j < TJ; ++j) {
-        if constexpr (BITS == 4) {
-          aop[j] = h == 0 ? op_from_nibbles(b.a[j].x, b.a[j].y) : op_from_nibbles(b.a[j].z, b.a[j].w);
-        } else {
-          const uint4 u = b.a[2 * j + h];
-          aop[j] = op_a8<WA8>(u.x, u.y, u.z, u.w);
-        }
+    for (int e = 0; e < 2; ++e) {
+      v4i aop;
+      if constexpr (BITS == 4) {
+        const uint4 u = a.v[h][0];
+        aop = e == 0 ? op_from_nibbles(u.x, u.y) : op_from_nibbles(u.z, u.w);
+      } else {
+        const uint4 u = a.v[h][e];
+        aop = op_a8<WA8>(u.x, u.y, u.z, u.w);
       }
 #pragma unroll
       for (int i = 0; i < TI; ++i) {
-        const v4i wop = h == 0 ? op_from_nibbles(b.w[i].x, b.w[i].y) : op_from_nibbles(b.w[i].z, b.w[i].w);
-#pragma unroll
-        for (int j = 0; j < TJ; ++j) acc[i][j] = mfma(wop, aop[j], acc[i][j]);
+        const uint4 u = w.v[h][i];
+        acc[i][j] = mfma(e == 0 ? op_from_nibbles(u.x, u.y) : op_from_nibbles(u.z, u.w), aop, acc[i][j]);
       }
     }
   };
 
-  // No barrier: the stage is the wavefront's own, and is refilled after its
-  // reads have returned, while the MFMAs run.
-  load(s_begin);
-  for (int s = s_begin; s < s_end; ++s) {
-    wait_vmcnt0_fence();
-    Half b0, b1;
-    read(0, b0);
-    read(1, b1);
+  // No barrier: the stage is the wavefront's own.  Small tiles refill it at
+  // once, after its reads have returned, while the MFMAs run.
+  if constexpr (!kStream) {
+    auto load_stage = [&](auto tail, int s) __attribute__((always_inline)) {
+      load_w(tail, s);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) load_a(tail, s, j);
+    };
+    auto load = [&](int s) __attribute__((always_inline)) {
+      if (s < min(s_end, half_stage)) load_stage(std::false_type{}, s);
+      else if (s < s_end) load_stage(std::true_type{}, s);
+    };
+    load(s_begin);
+    for (int s = s_begin; s < s_end; ++s) {
+      wait_vmcnt_fence<0>();
+      WFrag w;
+      AFrag a[TJ];
+      read_w(w);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) read_a(j, a[j]);
+      wait_lgkm0_fence();
+      load(s + 1);
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) compute(w, a[j], j, 0);
+      if (s < half_stage) {
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) compute(w, a[j], j, 1);
+      }
+    }
+  }
+  // Larger tiles: the stage is refilled part by part (the weights and the first activation block, then each of the other
+  // blocks), each part as soon as its reads have returned, and a part is read
+  // while the MFMAs of the one before run; so loads leave all the time.
+  // Step j of stage s reads part j + 1 of it (the last step part 0 of stage
+  // s + 1); more: whether stage s + 1 exists.
+  constexpr int kP0 = 2 * TI + kAB;   // loads of part 0
+  if (kStream && s_begin < s_end) {
+    part_w(s_begin);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) part_a(s_begin, j);
+    WFrag w[2];
+    AFrag a[2];
+    wait_vmcnt_fence<(TJ - 1) * kAB>();
+    read_w(w[0]);
+    read_a(0, a[0]);
     wait_lgkm0_fence();
-    load(s + 1);
-    compute(b0);
-    if (s < half_stage) compute(b1);
+    if (s_begin + 1 < s_end) {
+      part_w(s_begin + 1);
+      part_a(s_begin + 1, 0);
+    }
+    auto stage_steps = [&](auto morec, int s, const WFrag& wc, WFrag& wn, auto par) __attribute__((always_inline)) {
+      constexpr bool more = decltype(morec)::value;
+      constexpr int P = decltype(par)::value;   // a[P] holds block 0
+#pragma unroll
+      for (int j = 0; j < TJ; ++j) {
+        AFrag& ac = a[(P + j) & 1];
+        AFrag& an = a[(P + j + 1) & 1];
+        if (j + 1 < TJ) {
+          // In flight after it: blocks j + 2 .. of this stage, part 0 and blocks 1 .. j of the next.
+          if constexpr (more) wait_vmcnt_fence<(TJ - 2) * kAB + kP0>();
+          else wait_vmcnt_fence<0>();
+          read_a(j + 1, an);
+        } else if constexpr (more) {
+          wait_vmcnt_fence<(TJ - 1) * kAB>();
+          read_w(wn);
+          read_a(0, an);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        compute(wc, ac, j, 0);
+        if (more || s < half_stage) compute(wc, ac, j, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        wait_lgkm0_fence();
+        if constexpr (more) {
+          if (j + 1 < TJ) {
+            part_a(s + 1, j + 1);
+          } else if (s + 2 < s_end) {
+            part_w(s + 2);
+            part_a(s + 2, 0);
+          }
+        }
+      }
+    };
+    constexpr std::integral_constant<int, 0> p0{};
+    constexpr std::integral_constant<int, TJ & 1> p1{};
+    int s = s_begin;
+    for (; s + 2 < s_end; s += 2) {
+      stage_steps(std::true_type{}, s, w[0], w[1], p0);
+      stage_steps(std::true_type{}, s + 1, w[1], w[0], p1);
+    }
+    if (s + 1 < s_end) {
+      stage_steps(std::true_type{}, s, w[0], w[1], p0);
+      stage_steps(std::false_type{}, s + 1, w[1], w[0], p1);
+    } else {
+      stage_steps(std::false_type{}, s, w[0], w[1], p0);
+    }
   }
   __syncthreads();   // every wavefront is done with its stage
 
-  // Sum the partial tiles, WAVES fragments at a time: every wavefront adds
-  // one of them over all wavefronts and writes it.
-#pragma unroll
-  for (int f0 = 0; f0 < kFrags; f0 += WAVES) {
-    if (f0 > 0) __syncthreads();
-#pragma unroll
-    for (int g = 0; g < WAVES; ++g)
-      if (f0 + g < kFrags) part[g][wave][lane] = acc[(f0 + g) / TJ][(f0 + g) % TJ];
-    __syncthreads();
-    const int f = f0 + wave;
-    if (f >= kFrags) continue;
-    v4i tot = part[wave][0][lane];
+  // Sum the partial tiles, kPass blocks at a time.  Up to one block per
+  // wavefront, a wavefront adds one block over all wavefronts, each lane the
+  // four values it holds in its own (n .. n + 3 of one m).  More blocks go two
+  // at a time to a wavefront, a lane adding eight consecutive n of one m, so
+  // that the stores are 16 bytes.
+  auto total = [&](int g, int slot) __attribute__((always_inline)) {
+    v4i t = part[g][0][slot];
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) {
-      const v4i p = part[wave][w][lane];
-      tot.x += p.x; tot.y += p.y; tot.z += p.z; tot.w += p.w;
+      const v4i p = part[g][w][slot];
+      t.x += p.x; t.y += p.y; t.z += p.z; t.w += p.w;
     }
-    const int i = f / TJ, j = f - i * TJ;
-    const int m = m0 + 16 * j + fr, n = n0 + 16 * i + 4 * fg;
-    if (m >= M || n >= N) continue;
-    if constexpr (ACC_OUT) {
-      *reinterpret_cast<int4*>(acc_out + (size_t)m * N + n) =
-          make_int4(unscale<BITS>(tot.x), unscale<BITS>(tot.y), unscale<BITS>(tot.z), unscale<BITS>(tot.w));
-    } else {
-      const int off = ZP ? (1 << (BITS - 1)) - a_zeros[m] : 0;
-      const int4 wz = ZP ? *reinterpret_cast<const int4*>(w_sums + n) : make_int4(0, 0, 0, 0);
-      *reinterpret_cast<uint2*>(y + (size_t)m * N + n) =
-          dequant4z<BITS, ZP>(tot.x, tot.y, tot.z, tot.w, a_scales[m],
-                              *reinterpret_cast<const float4*>(w_scales + n), off, wz);
+    return t;
+  };
+  auto scaled = [&](v4i t, int m, int n) __attribute__((always_inline)) {
+    const int off = ZP ? (1 << (BITS - 1)) - a_zeros[m] : 0;
+    const int4 wz = ZP ? *reinterpret_cast<const int4*>(w_sums + n) : make_int4(0, 0, 0, 0);
+    return dequant4z<BITS, ZP>(t.x, t.y, t.z, t.w, a_scales[m],
+                               *reinterpret_cast<const float4*>(w_scales + n), off, wz);
+  };
+  auto unscaled = [&](v4i t) __attribute__((always_inline)) {
+    return make_int4(unscale<BITS>(t.x), unscale<BITS>(t.y), unscale<BITS>(t.z), unscale<BITS>(t.w));
+  };
+#pragma unroll
+  for (int f0 = 0; f0 < kFrags; f0 += kPass) {
+    if (f0 > 0) __syncthreads();
+#pragma unroll
+    for (int g = 0; g < kPass; ++g)
+      if (f0 + g < kFrags) part[g][wave][lane] = acc[(f0 + g) / TJ][(f0 + g) % TJ];
+    __syncthreads();
+    constexpr bool kPairs = kFrags > WAVES;
+    const int blocks = min(kPass, kFrags - f0);
+    for (int u = wave; u < (kPairs ? (blocks + 1) / 2 : blocks); u += WAVES) {
+      const int g = kPairs ? 2 * u + (lane >> 5) : u;
+      const int f = f0 + g, i = f / TJ, j = f - i * TJ;
+      const int q = kPairs ? (fg & 1) * 2 : fg;           // group of four n
+      const int m = m0 + 16 * j + fr, n = n0 + 16 * i + 4 * q;
+      if (g >= blocks || m >= M || n >= N) continue;      // whole blocks of n: N is a multiple of 16
+      const v4i t0 = total(g, 16 * q + fr);
+      if constexpr (kPairs) {
+        const v4i t1 = total(g, 16 * q + 16 + fr);
+        if constexpr (ACC_OUT) {
+          int32_t* o = acc_out + (size_t)m * N + n;
+          *reinterpret_cast<int4*>(o) = unscaled(t0);
+          *reinterpret_cast<int4*>(o + 4) = unscaled(t1);
+        } else {
+          const uint2 lo = scaled(t0, m, n), hi2 = scaled(t1, m, n + 4);
+          *reinterpret_cast<uint4*>(y + (size_t)m * N + n) = make_uint4(lo.x, lo.y, hi2.x, hi2.y);
+        }
+      } else if constexpr (ACC_OUT) {
+        *reinterpret_cast<int4*>(acc_out + (size_t)m * N + n) = unscaled(t0);
+      } else {
+        *reinterpret_cast<uint2*>(y + (size_t)m * N + n) = scaled(t0, m, n);
+      }
     }
   }
 }
@@ -256,22 +388,53 @@ void launch_cfg(const KsplitCall& c, hipStream_t stream) {
                      c.y, c.acc, c.a_zeros, c.w_sums);
 }
 
-// Tiles for M > 16, as TI, TJ and the wavefronts that split K: eight while
-// their stages and partial tiles fit a compute unit, else four.  The last two
-// only pay at 8 bits, where an activation row is twice a weight row's bytes.
+// Tiles for M > 16 (TI, TJ, the wavefronts that split K), and the estimated
+// microseconds of each: a start, then per round of `resident` workgroups a
+// compute unit a fixed part and the k loop, then what grows with every tile a
+// compute unit runs, with the weights' way from memory and with the output's.
+// Fitted to 288 shapes a bit width (M 20-1024, N 1024-28672, K 2048-28672;
+// weights cycling through 300 MB): the tile picked is within 2% of the best of
+// 20 on average.
 struct Tile {
-  int ti, tj, waves;
+  int ti, tj, waves, resident;
+  double start, round, round_k, tile_k, kn, mn;
 };
-constexpr Tile kTiles[] = {{1, 1, 8}, {1, 2, 8}, {2, 2, 8}, {2, 3, 8}, {4, 2, 8}, {4, 3, 8},
-                           {4, 4, 4}, {4, 6, 4}, {6, 4, 4}, {6, 6, 4}, {8, 4, 4}};
-constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
-constexpr int num_tiles(int bits) { return bits == 4 ? kNumTiles - 2 : kNumTiles; }
+constexpr Tile kTiles4[] = {
+    {1, 1, 8, 2, 2.38, 0.00, 9.85e-05, 1.08e-04, 2.16e-08, 2.90e-06},
+    {1, 2, 8, 1, 2.57, 0.00, 2.45e-04, 0.00e+00, 2.50e-08, 1.78e-06},
+    {2, 2, 8, 1, 2.52, 0.11, 3.35e-04, 0.00e+00, 2.93e-08, 1.51e-06},
+    {2, 3, 8, 1, 2.74, 0.27, 4.43e-04, 0.00e+00, 2.02e-08, 1.03e-06},
+    {2, 4, 8, 1, 1.79, 1.31, 5.76e-04, 0.00e+00, 1.70e-08, 1.07e-06},
+    {4, 3, 8, 1, 1.70, 1.83, 6.98e-04, 0.00e+00, 2.56e-08, 6.68e-07},
+    {2, 2, 4, 2, 2.75, 0.00, 3.36e-04, 1.77e-04, 2.87e-08, 5.92e-07},
+    {2, 3, 4, 3, 2.95, 0.00, 3.43e-04, 3.31e-04, 1.53e-08, 7.78e-07},
+    {2, 4, 4, 2, 3.02, 0.00, 4.13e-04, 3.16e-04, 1.81e-08, 9.85e-07},
+    {4, 4, 4, 2, 2.95, 0.86, 4.29e-04, 7.25e-04, 1.87e-08, 7.25e-07},
+    {8, 4, 4, 1, 1.68, 4.39, 1.57e-03, 0.00e+00, 1.81e-08, 4.62e-07},
+    {4, 8, 4, 1, 1.82, 3.80, 1.66e-03, 0.00e+00, 1.26e-08, 4.27e-07}};
+constexpr Tile kTiles8[] = {
+    {1, 1, 8, 1, 2.40, 0.00, 2.27e-04, 0.00e+00, 2.72e-08, 2.63e-06},
+    {1, 2, 8, 1, 2.37, 0.00, 3.68e-04, 0.00e+00, 2.37e-08, 2.57e-06},
+    {2, 2, 8, 1, 1.72, 0.71, 4.71e-04, 0.00e+00, 2.46e-08, 2.37e-06},
+    {2, 3, 8, 1, 1.73, 0.97, 6.26e-04, 0.00e+00, 1.35e-08, 1.63e-06},
+    {4, 3, 8, 1, 1.53, 1.57, 8.43e-04, 0.00e+00, 2.26e-08, 9.59e-07},
+    {2, 4, 4, 1, 2.56, 0.00, 7.39e-04, 0.00e+00, 1.60e-08, 1.03e-06},
+    {4, 2, 4, 2, 2.36, 0.41, 1.03e-04, 5.87e-04, 2.77e-08, 8.12e-07},
+    {4, 4, 4, 1, 1.51, 2.06, 1.01e-03, 0.00e+00, 1.69e-08, 8.48e-07},
+    {4, 6, 4, 1, 1.58, 2.73, 1.32e-03, 0.00e+00, 1.21e-08, 8.05e-07},
+    {4, 8, 4, 1, 1.65, 3.53, 1.63e-03, 0.00e+00, 1.82e-08, 6.65e-07},
+    {8, 4, 4, 1, 1.74, 3.79, 1.59e-03, 0.00e+00, 1.90e-08, 6.60e-07}};
+constexpr int num_tiles(int bits) {
+  return bits == 4 ? sizeof(kTiles4) / sizeof(kTiles4[0]) : sizeof(kTiles8) / sizeof(kTiles8[0]);
+}
+constexpr Tile tile_at(int bits, int i) { return bits == 4 ? kTiles4[i] : kTiles8[i]; }
 
 template <int BITS, bool ACC_OUT, bool WA8, bool ZP, int I = 0>
 void launch_tile(int tile, const KsplitCall& c, hipStream_t stream) {
   if constexpr (I < num_tiles(BITS)) {
+    constexpr Tile t = tile_at(BITS, I);
     if (tile == I)
-      launch_cfg<BITS, kTiles[I].ti, kTiles[I].tj, kTiles[I].waves, ACC_OUT, WA8, ZP, false>(c, stream);
+      launch_cfg<BITS, t.ti, t.tj, t.waves, ACC_OUT, WA8, ZP, false>(c, stream);
     else
       launch_tile<BITS, ACC_OUT, WA8, ZP, I + 1>(tile, c, stream);
   }
@@ -293,31 +456,30 @@ void launch_decode(const KsplitCall& c, hipStream_t stream) {
   else launch_cfg<BITS, 2, 1, 8, ACC_OUT, WA8, ZP, WDEC>(c, stream);
 }
 
-// Estimated microseconds of a tile: a start, then for each tile of the fullest
-// compute unit the bytes it pulls per k (TI and TJ terms), its MFMAs and its
-// reduction (TI * TJ terms), and the weights' way from memory.  Fitted to 15
-// tiles over 1024 shapes (M 17-1024, N 1024-28672, K 2048-14336); the
-// estimate is within 12% (one standard deviation) of the measured time.
-double tile_cost(Tile t, int64_t M, int64_t N, int K, int bits, int64_t cus) {
-  const int64_t tiles = ((M + 16 * t.tj - 1) / (16 * t.tj)) * ((N + 16 * t.ti - 1) / (16 * t.ti));
-  const double rounds = (double)((tiles + cus - 1) / cus);
-  const double area = (double)(t.ti * t.tj), k = (double)K;
-  if (bits == 4)
-    return 2.4 + rounds * (0.135 * area + k * (7.8e-5 * t.ti + 6.2e-5 * t.tj + 2.0e-5 * area)) +
-           2.4e-8 * k * (double)N;
-  return 1.9 + rounds * (0.2 * area + k * (7.8e-5 * t.ti + 1.85e-4 * t.tj + 1.7e-6 * area)) +
-         2.0e-8 * k * (double)N;
+// Tiles the fullest compute unit runs.
+int64_t tiles_per_cu(const Tile& t, int64_t M, int64_t N) {
+  const int64_t cus = device_cus();
+  return (((M + 16 * t.tj - 1) / (16 * t.tj)) * ((N + 16 * t.ti - 1) / (16 * t.ti)) + cus - 1) / cus;
 }
 
-int best_tile(int64_t M, int64_t N, int K, int bits, double* cost) {
-  const int64_t cus = device_cus();
-  int best = 0;
-  *cost = 0.0;
+double tile_cost(const Tile& t, int64_t M, int64_t N, int K) {
+  const int64_t q = tiles_per_cu(t, M, N);
+  const double rounds = (double)((q + t.resident - 1) / t.resident), k = (double)K;
+  return t.start + rounds * (t.round + k * t.round_k) + (double)q * k * t.tile_k + t.kn * k * (double)N +
+         t.mn * (double)M * (double)N;
+}
+
+// The tile with the lowest estimate; in_range: among those that run at most
+// three rounds, where the fitted shapes lie (-1: none).
+int best_tile(int64_t M, int64_t N, int K, int bits, bool in_range, double* cost) {
+  int best = -1;
   for (int i = 0; i < num_tiles(bits); ++i) {
-    const double t = tile_cost(kTiles[i], M, N, K, bits, cus);
-    if (i == 0 || t < *cost) {
+    const Tile t = tile_at(bits, i);
+    if (in_range && tiles_per_cu(t, M, N) > 3 * (t.resident > 2 ? t.resident : 2)) continue;
+    const double c = tile_cost(t, M, N, K);
+    if (best < 0 || c < *cost) {
       best = i;
-      *cost = t;
+      *cost = c;
     }
   }
   return best;
@@ -330,15 +492,16 @@ void launch_canonical(const KsplitCall& c, hipStream_t stream) {
     return;
   }
   double cost;
-  launch_tile<BITS, ACC_OUT, WA8, ZP>(best_tile(c.M, c.N, c.K, BITS, &cost), c, stream);
+  int tile = best_tile(c.M, c.N, c.K, BITS, true, &cost);
+  if (tile < 0) tile = best_tile(c.M, c.N, c.K, BITS, false, &cost);
+  launch_tile<BITS, ACC_OUT, WA8, ZP>(tile, c, stream);
 }
 
 }  // namespace
 
 double ksplit_cost(int64_t M, int64_t N, int K, int bits) {
   double cost;
-  best_tile(M, N, K, bits, &cost);
-  return cost;
+  return best_tile(M, N, K, bits, true, &cost) < 0 ? HUGE_VAL : cost;
 }
 
 hipError_t launch_ksplit(const KsplitCall& c, int bits, int weights, hipStream_t stream) {

@@ -37,6 +37,18 @@ CASES = [
     (97, 384, 11024, 4), (97, 384, 11024, 8),      # 6 x 4
     (129, 1408, 11024, 8),                         # 6 x 6
     (161, 896, 8208, 8),                           # 8 x 4
+    # four wavefronts (the stage refilled part by part from eight blocks on,
+    # but for 4 x 4 at 4 bits)
+    (18, 1152, 8608, 4), (20, 256, 8800, 8),       # 2 x 2, 4 x 2
+    (17, 1152, 8704, 8),                           # 4 x 2, one to two stages a wavefront
+    (33, 896, 9072, 4),                            # 2 x 3
+    (52, 1152, 12304, 4), (33, 1152, 4256, 8),     # 2 x 4
+    (50, 2944, 4112, 4),                           # 2 x 4 on eight
+    (512, 1408, 3728, 4), (50, 2432, 8224, 8),     # 4 x 4
+    (65, 1408, 12480, 8),                          # 4 x 6
+    (97, 1920, 12960, 8),                          # 4 x 8
+    (163, 2176, 8272, 8),                          # 8 x 4
+    (99, 4992, 12416, 4), (146, 6272, 8448, 4),    # 4 x 8, 8 x 4
 ]
 
 
