@@ -809,6 +809,307 @@ rq_seg_kernel(const __half* __restrict__ x, int M, int K, int J, uint8_t* __rest
   }
 }
 
+// ---------------------------------------------------------------------------
+// Rows of one Hadamard block of h = 28 * 2^J, J = 9 or 10 (K = h), fp16 in, codes
+// out.  The row stays in registers; LDS only moves it between layouts.
+//
+// Power-of-two part: a wavefront takes chunks of 1024 consecutive elements (one
+// slow index a at J = 10, two at J = 9), 16 a lane, and runs bits 0-3, 4-7 and
+// 8.. in three register layouts, through LDS of its own without a barrier:
+//   i = 16 lane + r,  256 (lane >> 4) + 16 r + (lane & 15),
+//   lane + 64 (r >> 2) + 256 (r & 3).
+//
+// 28-point part, y[b] = sum over a = 0 .. 27 in order of H28[a][b] z[a]: on the
+// fp32 matrix cores, 32 columns at a time, a chain of 14 MFMAs 32x32x2 whose
+// weights are +-1.  Such an MFMA adds its two products one after the other, each
+// sum rounded to nearest even (subnormals kept), so the chain is the pinned
+// sequence of additions bit for bit; the matrix cores take 28 cycles a column
+// where the vector ALU takes 40 (634 additions a column, 64 columns at a time).
+// The 28 x 2^J matrix passes through LDS in HALVES parts, so that two rows share
+// a compute unit and one's loads, barriers and stores run beside the other's
+// arithmetic (the general kernel holds one row of 28 x 1024).
+//
+// What bounds it: the vector ALU, about 25 operations an element, and the fp32
+// MFMAs, whose cycles add up (counters, 4096 x 28672: 192 and 115 of 354 thousand
+// cycles a SIMD).  4096 x 14336 at 8 bits 84.2 -> 64.0 us (2.75 TB/s), 4096 x
+// 28672 158.7 -> 124-129 us, with the FP6 output 186.1 -> 137-142 us; eight wavefronts a row
+// instead of sixteen 127.7 and 139.7 us.
+// ---------------------------------------------------------------------------
+struct H28Weights {
+  float w[4][64][4];   // [i / 4][l][i % 4]: H28[2 i + (l >> 5)][l & 31], rows 28 .. 31 zero
+  constexpr H28Weights() : w{} {
+    for (int l = 0; l < 64; ++l)
+      for (int i = 0; i < 14; ++i)
+        if ((l & 31) < 28) w[i / 4][l][i % 4] = (float)kH28.e[2 * i + (l >> 5)][l & 31];
+  }
+};
+__device__ const H28Weights kH28Weights{};
+struct H28Signs {
+  uint32_t m[64];      // bit i of [l]: H28[2 i + (l >> 5)][l & 31] < 0
+  constexpr H28Signs() : m{} {
+    for (int l = 0; l < 64; ++l)
+      for (int i = 0; i < 14; ++i)
+        if ((l & 31) < 28 && kH28.e[2 * i + (l >> 5)][l & 31] < 0) m[l] |= 1u << i;
+  }
+};
+__device__ const H28Signs kH28Signs{};
+
+// Keeps a wavefront's LDS accesses before and after on their sides (it executes
+// them in order).
+__device__ __forceinline__ void wave_lds_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+}
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+constexpr int kChunk = 1024, kChunkFloats = kChunk + kChunk / 16;
+
+template <int J, int WAVES, int HALVES>
+struct Rq28 {
+  static constexpr int kP = 1 << J, kK = 28 * kP;
+  static constexpr int kChunks = kK / kChunk;                    // 28 or 14
+  static constexpr int kMine = (kChunks + WAVES - 1) / WAVES;    // per wavefront, at most
+  static constexpr int kCols = kP / HALVES;                      // columns in LDS at a time
+  static constexpr int kRow = kCols + 32;                        // floats; the two rows a read touches use other banks
+  static constexpr int kGroups = kCols / 32 / WAVES;             // 32-column groups a wavefront, per part
+  static constexpr int kCodeRow = kP + 32;                       // bytes; four rows written together use other banks
+  static constexpr int kExchange = 28 * kRow * 4, kPrivate = WAVES * kChunkFloats * 4, kCodes = 28 * kCodeRow;
+  static constexpr int kLds = kExchange > kPrivate ? kExchange : kPrivate;
+  static_assert(kCols % (32 * WAVES) == 0 && kCodes <= kLds, "split");
+};
+
+template <int BITS, int J, int WAVES, int HALVES, bool FP6>
+__global__ void __launch_bounds__(WAVES * 64, WAVES / 2)
+rq28_kernel(const __half* __restrict__ x, int M, const uint8_t* __restrict__ signs,
+            uint8_t* __restrict__ codes, float* __restrict__ scales) {
+  using C = Rq28<J, WAVES, HALVES>;
+  constexpr int K = C::kK, kP = C::kP;
+  static_assert(!FP6 || BITS == 4, "FP6 output holds 4-bit codes");
+  __shared__ __attribute__((aligned(16))) uint8_t smem[C::kLds];
+  __shared__ float red[WAVES];
+  const int t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int mblk = (M + 31) >> 5;
+  const int row = FP6 ? fp6_row(blockIdx.x, mblk * 32) : (int)blockIdx.x;
+  if constexpr (FP6) {
+    if (row >= M) {   // padding row of the last block: zero codes
+      for (int q = t; q < K / 32; q += WAVES * 64) {
+        uint8_t* d = codes + fp6_slot(row, 32 * q, mblk);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) *reinterpret_cast<uint2*>(d + 512 * c) = make_uint2(0, 0);
+      }
+      return;
+    }
+  }
+  const __half* xr = x + (size_t)row * K;
+
+  // Chunks wave, wave + WAVES, ...: all loads first.
+  uint4 in[C::kMine][2];
+#pragma unroll
+  for (int q = 0; q < C::kMine; ++q) {
+    const int e = min(wave + q * WAVES, C::kChunks - 1) * kChunk + 16 * lane;
+    in[q][0] = *reinterpret_cast<const uint4*>(xr + e);
+    in[q][1] = *reinterpret_cast<const uint4*>(xr + e + 8);
+  }
+  float v[C::kMine][16];
+  float* priv = reinterpret_cast<float*>(smem) + wave * kChunkFloats;
+#pragma unroll
+  for (int q = 0; q < C::kMine; ++q) {
+    const int chunk = wave + q * WAVES;
+    if (chunk >= C::kChunks) continue;
+    widen8(in[q][0], v[q]);
+    widen8(in[q][1], v[q] + 8);
+    if (signs) {
+      const uint8_t* sb = signs + (chunk * kChunk + 16 * lane) / 8;
+      apply_sign_bits<16>(v[q], (uint32_t)sb[0] | ((uint32_t)sb[1] << 8));
+    }
+    stages16<0, 4>(v[q]);
+    float* p1 = priv + seg_off(16 * lane);
+    wave_lds_order();
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      *reinterpret_cast<float4*>(p1 + 4 * u) = make_float4(v[q][4 * u], v[q][4 * u + 1], v[q][4 * u + 2], v[q][4 * u + 3]);
+    wave_lds_order();
+    float* p2 = priv + seg_off(256 * (lane >> 4) + (lane & 15));
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[q][r] = p2[16 * r + 4 * (r >> 2)];
+    stages16<0, 4>(v[q]);
+    wave_lds_order();
+#pragma unroll
+    for (int r = 0; r < 16; ++r) p2[16 * r + 4 * (r >> 2)] = v[q][r];
+    wave_lds_order();
+    const float* p3 = priv + lane;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) v[q][r] = p3[68 * (r >> 2) + 272 * (r & 3)];
+    stages16<0, J - 8>(v[q]);
+  }
+
+  // Column parts: into LDS as rows a, then 28 points of 32 columns an MFMA chain.
+  // The MFMAs' weights as loads from the caches are two vector operations fewer
+  // an element than made from a bit mask (4096 rows of 28 x 512 at 8 bits: 64.0
+  // against 67.8 us); at 28 x 1024 their registers cost more than that (FP6
+  // output 144.7 against 136.9 us).
+  constexpr bool kLoadWeights = J == 9;
+  float hw[16];
+  uint32_t hs = 0;
+  if constexpr (kLoadWeights) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 u = *reinterpret_cast<const float4*>(kH28Weights.w[i][lane]);
+      hw[4 * i] = u.x; hw[4 * i + 1] = u.y; hw[4 * i + 2] = u.z; hw[4 * i + 3] = u.w;
+    }
+  } else {
+    hs = kH28Signs.m[lane];
+  }
+  float* ex = reinterpret_cast<float*>(smem);
+  v16f d[HALVES * C::kGroups];
+#pragma unroll
+  for (int part = 0; part < HALVES; ++part) {
+    __syncthreads();   // the private pieces, or the last part, are read
+#pragma unroll
+    for (int q = 0; q < C::kMine; ++q) {
+      const int chunk = wave + q * WAVES;
+      if (chunk >= C::kChunks) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int hi = 64 * (r >> 2) + 256 * (r & 3);       // i = lane + hi
+        if ((hi & (kP - 1)) / C::kCols != part) continue;
+        const int a0 = hi >> J;                             // 0, or 1 in a chunk's upper half at J = 9
+        ex[((chunk << (10 - J)) + a0) * C::kRow + (hi & (C::kCols - 1)) + lane] = v[q][r];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < C::kGroups; ++g) {
+      const float* z = ex + (lane >> 5) * C::kRow + 32 * (wave * C::kGroups + g) + (lane & 31);
+      float zz[14];
+#pragma unroll
+      for (int i = 0; i < 14; ++i) zz[i] = z[2 * i * C::kRow];
+      v16f acc = {};
+#pragma unroll
+      for (int i = 0; i < 14; ++i) {
+        const float hv = kLoadWeights ? hw[i] : __uint_as_float(0x3F800000u | ((hs << (31 - i)) & 0x80000000u));
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(hv, zz[i], acc, 0, 0, 0);
+      }
+      d[part * C::kGroups + g] = acc;
+    }
+  }
+
+  // Lane l holds column l & 31 of its groups, rows b = 8 (i >> 2) + 4 (l >> 5) +
+  // (i & 3) in register i; rows 28 .. 31 do not exist.
+  const int bl = 4 * (lane >> 5);
+  float tmax = 0.0f;
+#pragma unroll
+  for (int g = 0; g < HALVES * C::kGroups; ++g)
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (i % 2 == 0 && (i < 12 || bl == 0)) tmax = fmaxf(fmaxf(fabsf(d[g][i]), fabsf(d[g][i + 1])), tmax);
+  tmax = wave_max_nonneg(tmax);
+  if (lane == 0) red[wave] = tmax;
+  __syncthreads();   // also: every column is read
+  float amax = red[0];
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) amax = fmaxf(amax, red[w]);
+  constexpr float qmax = (float)((1 << (BITS - 1)) - 1);
+  const float sc = amax / qmax;                 // IEEE division
+  const float rc = sc != 0.0f ? 1.0f / sc : 0.0f;
+  if (t == 0) scales[row] = sc;
+
+  // Codes as bytes into LDS: each lane packs four rows of its column, and a quad
+  // of lanes (four columns) transposes, so that a lane writes four columns of one row.
+  const int ql = lane & 3;
+  const uint32_t sel = 0x0c0c0400u + 0x0101u * ql;   // [w0 byte ql, w1 byte ql, 0, 0] of perm(w1, w0)
+#pragma unroll
+  for (int g = 0; g < HALVES * C::kGroups; ++g) {
+    const int c0 = (g / C::kGroups) * C::kCols + 32 * (wave * C::kGroups + g % C::kGroups) + (lane & 28);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      uint32_t bt[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bt[i] = round_bits(d[g][4 * u + i], sc, rc);
+      const int w = (int)low_bytes(bt[0], bt[1], bt[2], bt[3]);
+      const uint32_t w0 = (uint32_t)__builtin_amdgcn_mov_dpp(w, 0x00, 0xF, 0xF, false);
+      const uint32_t w1 = (uint32_t)__builtin_amdgcn_mov_dpp(w, 0x55, 0xF, 0xF, false);
+      const uint32_t w2 = (uint32_t)__builtin_amdgcn_mov_dpp(w, 0xAA, 0xF, 0xF, false);
+      const uint32_t w3 = (uint32_t)__builtin_amdgcn_mov_dpp(w, 0xFF, 0xF, 0xF, false);
+      const uint32_t lo = __builtin_amdgcn_perm(w1, w0, sel), hi = __builtin_amdgcn_perm(w3, w2, sel);
+      if (u < 3 || bl == 0)
+        *reinterpret_cast<uint32_t*>(smem + (8 * u + bl + ql) * C::kCodeRow + c0) = lo | (hi << 16);
+    }
+  }
+  __syncthreads();
+
+  // Out, 32 codes (16 at 8 bits) a thread at a time.
+  constexpr int kOut = BITS == 4 ? 32 : 16;
+  for (int e = kOut * t; e < K; e += kOut * WAVES * 64) {
+    const uint8_t* src = smem + (e >> J) * C::kCodeRow + (e & (kP - 1));
+    const uint4 u0 = *reinterpret_cast<const uint4*>(src);
+    if constexpr (BITS == 8) {
+      *reinterpret_cast<uint4*>(codes + (size_t)row * K + e) = u0;
+    } else {
+      const uint4 u1 = *reinterpret_cast<const uint4*>(src + 16);
+      const uint32_t w[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+      if constexpr (FP6) {
+        // Biased codes u = c + 8 as the fp16 values 1024 + u, then c / 2 =
+        // (1024 + u) / 2 - 516, every step exact.
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+        typedef unsigned int v16u __attribute__((ext_vector_type(16)));
+        v16u all;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const uint32_t b = (w[i] & 0x0F0F0F0Fu) ^ 0x08080808u;
+#pragma unroll
+          for (int k = 0; k < 2; ++k) {
+            const uint32_t pair = __builtin_amdgcn_perm(0x64646464u, b, k == 0 ? 0x04010400u : 0x04030402u);
+            const h2 hv = __builtin_bit_cast(h2, pair) * (_Float16)0.5f - (_Float16)516.0f;
+            all[2 * i + k] = __builtin_bit_cast(uint32_t, hv);
+          }
+        }
+        const f6_v6i f = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(__builtin_bit_cast(f6_v32h, all), 1.0f);
+        uint8_t* o = codes + fp6_slot(row, e, mblk);
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+          *reinterpret_cast<uint2*>(o + 512 * c) = make_uint2((uint32_t)f[2 * c], (uint32_t)f[2 * c + 1]);
+      } else {
+        uint32_t o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          uint32_t p0 = w[2 * i] & 0x0F0F0F0Fu, p1 = w[2 * i + 1] & 0x0F0F0F0Fu;
+          p0 |= p0 >> 4;
+          p1 |= p1 >> 4;
+          o[i] = __builtin_amdgcn_perm(p1, p0, 0x06040200u);
+        }
+        *reinterpret_cast<uint4*>(codes + (size_t)row * (K / 2) + e / 2) = make_uint4(o[0], o[1], o[2], o[3]);
+      }
+    }
+  }
+}
+
+template <int BITS, int J, int WAVES, int HALVES, bool FP6>
+hipError_t launch_rq28_t(const __half* x, int64_t M, const uint8_t* signs, uint8_t* codes, float* scales,
+                         hipStream_t stream) {
+  const int64_t grid = FP6 ? (M + 31) / 32 * 32 : M;
+  hipLaunchKernelGGL((rq28_kernel<BITS, J, WAVES, HALVES, FP6>), dim3((unsigned)grid), dim3(WAVES * 64), 0,
+                     stream, x, (int)M, signs, codes, scales);
+  return hipGetLastError();
+}
+
+// Rows it takes: more than 64 of 28 x 512 (256 rows 7.2 us, against 9.8 us on
+// the general kernel's 256 threads a row; its 1024 threads for fewer rows are as
+// fast, 6.6 and 6.7 us), and more rows than compute units of 28 x 1024 (256 rows
+// 11.3 us against 10.6 us, 300 rows 17.9 us against 19.0 us).
+bool use_rq28(int64_t M, int K, HadSplit hs) {
+  return hs.f == 28 && K == (28 << hs.j) && ((hs.j == 9 && M > kFewRows) || (hs.j == 10 && M > device_cus()));
+}
+
+template <int BITS, bool FP6>
+hipError_t launch_rq28(const __half* x, int64_t M, int J, const uint8_t* signs, uint8_t* codes, float* scales,
+                       hipStream_t stream) {
+  return J == 9 ? launch_rq28_t<BITS, 9, 16, 1, FP6>(x, M, signs, codes, scales, stream)
+                : launch_rq28_t<BITS, 10, 16, 2, FP6>(x, M, signs, codes, scales, stream);
+}
+
 size_t pow2_lds_bytes(int K) { return (size_t)((K + kSeg - 1) / kSeg) * kSegFloats * sizeof(float); }
 
 template <typename Tin, int BITS, bool WEIGHT, int J, bool STATS, bool FP6>
@@ -885,6 +1186,10 @@ hipError_t launch_rq(const Tin* x, int64_t M, int K, HadSplit hs, uint8_t* codes
         return launch_seg<BITS>(reinterpret_cast<const __half*>(x), M, K, hs.j, codes, scales,
                                 stream);
     }
+  }
+  if constexpr (!WEIGHT && !STATS && sizeof(Tin) == 2) {
+    if (use_rq28(M, K, hs))
+      return launch_rq28<BITS, FP6>(reinterpret_cast<const __half*>(x), M, hs.j, signs, codes, scales, stream);
   }
   if (hs.f == 28)
     return dispatch_j<Tin, BITS, WEIGHT, 28, STATS, FP6>(hs.j, x, M, K, signs, codes, scales, st,
