@@ -25,6 +25,9 @@ namespace {
 
 using namespace f6;
 
+// Four scales from a pointer that is 4-byte aligned, as the entry point takes it.
+typedef float v4f_dw __attribute__((ext_vector_type(4), aligned(4)));
+
 // Waits that no memory access moves across.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt_fence() {
@@ -168,8 +171,9 @@ qgemm_fp6_ksplit(const uint8_t* __restrict__ a6, const float* __restrict__ a_sca
         *reinterpret_cast<int4*>(o + 8) = make_int4((int)t1.x, (int)t1.y, (int)t1.z, (int)t1.w);
       } else {
         const float as = a_scales[min(m, M - 1)];
-        const float4 ws0 = *reinterpret_cast<const float4*>(w_scales + nb + 4 * fg);
-        const float4 ws1 = *reinterpret_cast<const float4*>(w_scales + nb + 8 + 4 * fg);
+        const v4f_dw v0 = *reinterpret_cast<const v4f_dw*>(w_scales + nb + 4 * fg);
+        const v4f_dw v1 = *reinterpret_cast<const v4f_dw*>(w_scales + nb + 8 + 4 * fg);
+        const float4 ws0 = make_float4(v0.x, v0.y, v0.z, v0.w), ws1 = make_float4(v1.x, v1.y, v1.z, v1.w);
         const uint2 x0 = f6_dequant4(t0.x, t0.y, t0.z, t0.w, as, ws0);
         const uint2 x1 = f6_dequant4(t1.x, t1.y, t1.z, t1.w, as, ws1);
         const auto s0 = __builtin_amdgcn_permlane32_swap(x0.x, x1.x, false, false);

@@ -47,3 +47,18 @@ def test_fp6_ksplit_tiles(M, N, K):
     y = dptq.qlinear_fp6(a6, d[2], w6, d[3], M, K, N).cpu().numpy()
     bad = np.nonzero(y.view(np.uint16) != oracle_y(acc_ref, a_s, w_s).view(np.uint16))
     assert bad[0].size == 0, f"{bad[0].size} outputs differ, first at {bad[0][0]},{bad[1][0]}"
+
+
+@pytest.mark.parametrize("off", [1, 2, 3])
+def test_fp6_ksplit_scales_off_16_bytes(off):
+    # The scales may start at any multiple of 4 bytes.
+    M, N, K = 500, 2064, 256
+    rng = np.random.default_rng(off)
+    a = workloads.random_weight_bytes(rng, M, K)
+    w = workloads.random_weight_bytes(rng, N, K)
+    a6, w6 = (dptq.pack_fp6(torch.from_numpy(v).cuda()) for v in (a, w))
+    a_s = torch.from_numpy(workloads.random_scales(rng, M + off, 1e-3, 1.0)).cuda()
+    w_s = torch.from_numpy(workloads.random_scales(rng, N + off, 1e-5, 1e-4)).cuda()
+    y = dptq.qlinear_fp6(a6, a_s[off:], w6, w_s[off:], M, K, N)
+    ref = dptq.qlinear_fp6(a6, a_s[off:].clone(), w6, w_s[off:].clone(), M, K, N)
+    assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
