@@ -173,13 +173,29 @@ void* stream_of(const at::Tensor& t) {
   return p;
 }
 
-// Calls f without the interpreter lock and raises on a nonzero status.
-template <typename F>
-void call(const char* what, F f) {
+// The interpreter lock released for a scope, also when an exception leaves it.
+class Unlocked {
+ public:
+  Unlocked() : state_(PyEval_SaveThread()) {}
+  ~Unlocked() { PyEval_RestoreThread(state_); }
+  Unlocked(const Unlocked&) = delete;
+
+ private:
+  PyThreadState* state_;
+};
+
+// Calls the C entry f(args..., stream) on the current stream of t's device,
+// without the interpreter lock, and raises on a nonzero status.  The arguments,
+// data pointers among them, are values by then: what a tensor without storage
+// throws leaves with the lock held.
+template <typename F, typename... A>
+void call(const char* what, const at::Tensor& t, F f, A... args) {
+  void* stream = stream_of(t);
   int st;
-  Py_BEGIN_ALLOW_THREADS
-  st = f();
-  Py_END_ALLOW_THREADS
+  {
+    Unlocked unlocked;
+    st = f(args..., stream);
+  }
   if (st == DPTQ_OK) return;
   PyObject* r = PyObject_CallFunction(g_raise, "is", st, what);
   Py_XDECREF(r);
@@ -221,16 +237,11 @@ PyObject* rotate_quant(PyObject* const* a) {
   Out scales(a[4], "scales", at::kFloat, {M}, x);
   const at::Tensor* signs = signs_of(a[5], K, x);
   const int32_t h = integer32(a[1]);
-  void* st = stream_of(x);
   if (!signs)
-    call("dptq_rotate_quant", [&] {
-      return dptq_rotate_quant(ptr(x), M, K, h, bits, codes.ptr(), scales.ptr<float>(), st);
-    });
+    call("dptq_rotate_quant", x, dptq_rotate_quant, ptr(x), M, K, h, bits, codes.ptr(), scales.ptr<float>());
   else
-    call("dptq_rotate_quant_ex", [&] {
-      return dptq_rotate_quant_ex(ptr(x), M, K, h, bits, ptr<uint8_t>(*signs), DPTQ_LAYOUT_PACKED,
-                                  codes.ptr(), scales.ptr<float>(), st);
-    });
+    call("dptq_rotate_quant_ex", x, dptq_rotate_quant_ex, ptr(x), M, K, h, bits, ptr<uint8_t>(*signs),
+         DPTQ_LAYOUT_PACKED, codes.ptr(), scales.ptr<float>());
   return tuple(codes, scales);
 }
 
@@ -243,16 +254,12 @@ PyObject* rotate_quant_fp6(PyObject* const* a) {
   Out scales(a[3], "scales", at::kFloat, {M}, x);
   const at::Tensor* signs = signs_of(a[4], K, x);
   const int32_t h = integer32(a[1]);
-  void* st = stream_of(x);
   if (!signs)
-    call("dptq_rotate_quant_fp6", [&] {
-      return dptq_rotate_quant_fp6(ptr(x), M, K, h, out.ptr<uint8_t>(), scales.ptr<float>(), st);
-    });
+    call("dptq_rotate_quant_fp6", x, dptq_rotate_quant_fp6, ptr(x), M, K, h, out.ptr<uint8_t>(),
+         scales.ptr<float>());
   else
-    call("dptq_rotate_quant_ex", [&] {
-      return dptq_rotate_quant_ex(ptr(x), M, K, h, 4, ptr<uint8_t>(*signs), DPTQ_LAYOUT_FP6, out.ptr(),
-                                  scales.ptr<float>(), st);
-    });
+    call("dptq_rotate_quant_ex", x, dptq_rotate_quant_ex, ptr(x), M, K, h, 4, ptr<uint8_t>(*signs),
+         DPTQ_LAYOUT_FP6, out.ptr(), scales.ptr<float>());
   return tuple(out, scales);
 }
 
@@ -266,11 +273,8 @@ PyObject* rotate_quant_range(PyObject* const* a) {
   Out scales(a[4], "scales", at::kFloat, {M}, x);
   Out zeros(a[5], "zeros", at::kInt, {M}, x);
   const int32_t h = integer32(a[1]);
-  void* st = stream_of(x);
-  call("dptq_rotate_quant_range", [&] {
-    return dptq_rotate_quant_range(ptr(x), M, K, h, bits, codes.ptr(), scales.ptr<float>(),
-                                   zeros.ptr<int32_t>(), st);
-  });
+  call("dptq_rotate_quant_range", x, dptq_rotate_quant_range, ptr(x), M, K, h, bits, codes.ptr(),
+       scales.ptr<float>(), zeros.ptr<int32_t>());
   return tuple(codes, scales, zeros);
 }
 
@@ -296,17 +300,12 @@ PyObject* qlinear(PyObject* const* a) {
   const at::Tensor& ws = tensor_of(a[4], "w_scales", at::kFloat, {g.N});
   Out y(a[5], "y", at::kHalf, {g.M, g.N}, g.codes);
   const int32_t kernel = integer32(a[6]);
-  void* st = stream_of(g.codes);
   if (kernel == DPTQ_GEMM_AUTO)
-    call("dptq_qlinear", [&] {
-      return dptq_qlinear(ptr(g.codes), ptr<float>(as), g.M, g.K, bits, ptr<uint8_t>(g.w), ptr<float>(ws), g.N,
-                          y.ptr(), st);
-    });
+    call("dptq_qlinear", g.codes, dptq_qlinear, ptr(g.codes), ptr<float>(as), g.M, g.K, bits,
+         ptr<uint8_t>(g.w), ptr<float>(ws), g.N, y.ptr());
   else
-    call("dptq_qlinear_kernel", [&] {
-      return dptq_qlinear_kernel(ptr(g.codes), ptr<float>(as), g.M, g.K, bits, ptr<uint8_t>(g.w),
-                                 ptr<float>(ws), g.N, y.ptr(), nullptr, kernel, st);
-    });
+    call("dptq_qlinear_kernel", g.codes, dptq_qlinear_kernel, ptr(g.codes), ptr<float>(as), g.M, g.K, bits,
+         ptr<uint8_t>(g.w), ptr<float>(ws), g.N, y.ptr(), nullptr, kernel);
   return y.release();
 }
 
@@ -317,11 +316,8 @@ PyObject* qlinear_a8(PyObject* const* a) {
   const at::Tensor& ws = tensor_of(a[3], "w_scales", at::kFloat, {g.N});
   Out y(a[4], "y", at::kHalf, {g.M, g.N}, g.codes);
   const int32_t kernel = integer32(a[5]);
-  void* st = stream_of(g.codes);
-  call("dptq_qlinear_a8", [&] {
-    return dptq_qlinear_a8(ptr(g.codes), ptr<float>(as), g.M, g.K, ptr<uint8_t>(g.w), ptr<float>(ws), g.N,
-                           y.ptr(), kernel, st);
-  });
+  call("dptq_qlinear_a8", g.codes, dptq_qlinear_a8, ptr(g.codes), ptr<float>(as), g.M, g.K, ptr<uint8_t>(g.w),
+       ptr<float>(ws), g.N, y.ptr(), kernel);
   return y.release();
 }
 
@@ -340,11 +336,8 @@ PyObject* qlinear_decode_native(PyObject* const* a) {
   const at::Tensor& as = tensor_of(a[1], "a_scales", at::kFloat, {M});
   const at::Tensor& ws = tensor_of(a[4], "w_scales", at::kFloat, {N});
   Out y(a[5], "y", at::kHalf, {M, N}, codes);
-  void* st = stream_of(codes);
-  call("dptq_qlinear_decode_native", [&] {
-    return dptq_qlinear_decode_native(ptr(codes), ptr<float>(as), M, K, bits, ptr<uint8_t>(w), ptr<float>(ws), N,
-                                      y.ptr(), nullptr, st);
-  });
+  call("dptq_qlinear_decode_native", codes, dptq_qlinear_decode_native, ptr(codes), ptr<float>(as), M, K,
+       bits, ptr<uint8_t>(w), ptr<float>(ws), N, y.ptr(), nullptr);
   return y.release();
 }
 
@@ -356,11 +349,8 @@ PyObject* qlinear_fp6(PyObject* const* a) {
   const at::Tensor& as = tensor_of(a[1], "a_scales", at::kFloat, {M});
   const at::Tensor& ws = tensor_of(a[3], "w_scales", at::kFloat, {N});
   Out y(a[7], "y", at::kHalf, {M, N}, a6);
-  void* st = stream_of(a6);
-  call("dptq_qlinear_fp6", [&] {
-    return dptq_qlinear_fp6(ptr<uint8_t>(a6), ptr<float>(as), M, K, ptr<uint8_t>(w6), ptr<float>(ws), N, y.ptr(),
-                            nullptr, st);
-  });
+  call("dptq_qlinear_fp6", a6, dptq_qlinear_fp6, ptr<uint8_t>(a6), ptr<float>(as), M, K, ptr<uint8_t>(w6),
+       ptr<float>(ws), N, y.ptr(), nullptr);
   return y.release();
 }
 
@@ -378,11 +368,8 @@ PyObject* qlinear_decode_fused(PyObject* const* a) {
   Out codes(a[6], "codes", code_dtype(bits), {M, bits == 4 ? K / 2 : K}, x);
   Out scales(a[7], "scales", at::kFloat, {M}, x);
   const int32_t h = integer32(a[1]), mode = integer32(a[8]);
-  void* st = stream_of(x);
-  call("dptq_qlinear_decode_fused", [&] {
-    return dptq_qlinear_decode_fused(ptr(x), M, K, h, bits, ptr<uint8_t>(w), ptr<float>(ws), N, y.ptr(),
-                                     codes.ptr(), scales.ptr<float>(), mode, st);
-  });
+  call("dptq_qlinear_decode_fused", x, dptq_qlinear_decode_fused, ptr(x), M, K, h, bits, ptr<uint8_t>(w),
+       ptr<float>(ws), N, y.ptr(), codes.ptr(), scales.ptr<float>(), mode);
   return tuple(y, codes, scales);
 }
 
@@ -402,11 +389,8 @@ PyObject* qlinear_range(PyObject* const* a) {
   const at::Tensor& ws = tensor_of(a[5], "w_scales", at::kFloat, {N});
   const at::Tensor& sums = tensor_of(a[6], "w_sums", at::kInt, {N});
   Out y(a[7], "y", at::kHalf, {M, N}, codes);
-  void* st = stream_of(codes);
-  call("dptq_qlinear_range", [&] {
-    return dptq_qlinear_range(ptr(codes), ptr<float>(s), ptr<int32_t>(z), M, K, bits, ptr<uint8_t>(w),
-                              ptr<float>(ws), ptr<int32_t>(sums), N, y.ptr(), st);
-  });
+  call("dptq_qlinear_range", codes, dptq_qlinear_range, ptr(codes), ptr<float>(s), ptr<int32_t>(z), M, K,
+       bits, ptr<uint8_t>(w), ptr<float>(ws), ptr<int32_t>(sums), N, y.ptr());
   return y.release();
 }
 
@@ -423,11 +407,8 @@ PyObject* residual_dynamics(PyObject* const* a) {
   const int32_t h = integer32(a[2]);
   const double eps = PyFloat_AsDouble(a[4]);
   if (eps == -1.0 && PyErr_Occurred()) throw Raised{};
-  void* st = stream_of(x);
-  call("dptq_residual_dynamics", [&] {
-    return dptq_residual_dynamics(ptr(x), ptr(dx), T, K, h, bits, (float)eps, jr.ptr<float>(), snr.ptr<float>(),
-                                  means.ptr<double>(), st);
-  });
+  call("dptq_residual_dynamics", x, dptq_residual_dynamics, ptr(x), ptr(dx), T, K, h, bits, (float)eps,
+       jr.ptr<float>(), snr.ptr<float>(), means.ptr<double>());
   return tuple(jr, snr, means);
 }
 
@@ -441,10 +422,8 @@ PyObject* kv_quant(PyObject* const* a) {
   Out scales(a[3], "scales", at::kFloat, {T, D / group}, kv);
   Out mins(a[4], "mins", at::kFloat, {T, D / group}, kv);
   const int32_t g = integer32(a[1]);
-  void* st = stream_of(kv);
-  call("dptq_kv_quant", [&] {
-    return dptq_kv_quant(ptr(kv), T, D, g, codes.ptr<uint8_t>(), scales.ptr<float>(), mins.ptr<float>(), st);
-  });
+  call("dptq_kv_quant", kv, dptq_kv_quant, ptr(kv), T, D, g, codes.ptr<uint8_t>(), scales.ptr<float>(),
+       mins.ptr<float>());
   return tuple(codes, scales, mins);
 }
 
@@ -458,10 +437,8 @@ PyObject* kv_dequant(PyObject* const* a) {
   const at::Tensor& mins = tensor_of(a[2], "mins", at::kFloat, {T, D / group});
   Out out(a[4], "out", at::kHalf, {T, D}, codes);
   const int32_t g = integer32(a[3]);
-  void* st = stream_of(codes);
-  call("dptq_kv_dequant", [&] {
-    return dptq_kv_dequant(ptr<uint8_t>(codes), ptr<float>(scales), ptr<float>(mins), T, D, g, out.ptr(), st);
-  });
+  call("dptq_kv_dequant", codes, dptq_kv_dequant, ptr<uint8_t>(codes), ptr<float>(scales), ptr<float>(mins),
+       T, D, g, out.ptr());
   return out.release();
 }
 

@@ -1,6 +1,9 @@
 """The argument checks of the Python binding's per-call functions: what they
 refuse, with which error, and that buffers passed in are the ones returned."""
 
+import subprocess
+import sys
+
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -21,6 +24,45 @@ def test_refusals(call, error, text):
     dptq.lib()
     with pytest.raises(error, match=text.replace("(", r"\(")):
         call()
+
+
+# Tensors without storage (function transforms wrap theirs), on fake GPU tensors
+# and a fixed stream so that no GPU is needed.  In a process of its own: an
+# exception that leaves the native call without the interpreter lock ends it.
+_NO_STORAGE = """
+import torch, paper_2606_12487_amd as dptq
+from torch._subclasses import FakeTensorMode
+dptq._binding().init(dptq._check, lambda device: 0)
+with FakeTensorMode():
+    empty = lambda dtype, *shape: torch.empty(shape, dtype=dtype, device="cuda")
+    x, s, w = empty(torch.float16, 3, 128), empty(torch.float32, 3), empty(torch.uint8, 16, 64)
+    c, ws, y = empty(torch.uint8, 3, 64), empty(torch.float32, 16), empty(torch.float16, 3, 16)
+    a6, w6 = empty(torch.uint8, 3072), empty(torch.uint8, 3072)
+    calls = [
+        lambda: torch.vmap(lambda r: dptq.rotate_quant(r, 128, 4, c, s))(x[None]),
+        lambda: torch.func.vjp(lambda r: dptq.rotate_quant(r, 128, 4)[1], x),
+        lambda: torch.func.vjp(lambda r: dptq.rotate_quant_fp6(r, 128)[1], x),
+        lambda: torch.func.vjp(lambda r: dptq.rotate_quant_range(r, 128, 8)[1], x),
+        lambda: torch.func.vjp(lambda r: dptq.qlinear(c, r, 4, w, ws), s),
+        lambda: torch.func.vjp(lambda r: dptq.qlinear_fp6(a6, r, w6, ws, 3, 128, 16, y), s),
+        lambda: torch.func.vjp(lambda r: dptq.qlinear_decode_fused(r, 128, 4, w, ws)[0], x),
+        lambda: torch.func.vjp(lambda r: dptq.residual_dynamics(x, r, 128)[0], x),
+        lambda: torch.func.vjp(lambda r: dptq.kv_quant(r)[1], x),
+    ]
+    for call in calls:
+        try:
+            call()
+            print("no error")
+        except RuntimeError as e:
+            print(e)
+"""
+
+
+def test_tensors_without_storage_raise():
+    r = subprocess.run([sys.executable, "-c", _NO_STORAGE], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, (r.returncode, r.stdout, r.stderr[-2000:])
+    lines = [line for line in r.stdout.splitlines() if line]
+    assert lines == ["Cannot access data pointer of Tensor that doesn't have storage"] * 9, r.stdout
 
 
 @pytest.mark.gpu
