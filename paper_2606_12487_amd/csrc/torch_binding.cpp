@@ -86,18 +86,21 @@ int64_t dim(const at::Tensor& t, int i) {
   return t.size(i);
 }
 
-// int(o)
-int64_t integer(PyObject* o) {
-  if (PyLong_CheckExact(o)) {
-    const int64_t v = PyLong_AsLongLong(o);
-    if (v == -1 && PyErr_Occurred()) throw Raised{};
-    return v;
+// An integer argument; any_number: also another number of an integer's value.
+int64_t integer(PyObject* o, const char* name, bool any_number = false) {
+  PyObject* n = PyIndex_Check(o) ? PyNumber_Index(o) : any_number && PyNumber_Check(o) ? PyNumber_Long(o) : nullptr;
+  if (!n) {
+    if (!PyErr_Occurred()) PyErr_Format(PyExc_TypeError, "%s must be an integer, got %R", name, o);
+    throw Raised{};
   }
-  PyObject* n = PyNumber_Long(o);
-  if (!n) throw Raised{};
+  const int eq = PyIndex_Check(o) ? 1 : PyObject_RichCompareBool(o, n, Py_EQ);
   const int64_t v = PyLong_AsLongLong(n);
   Py_DECREF(n);
-  if (v == -1 && PyErr_Occurred()) throw Raised{};
+  if (PyErr_Occurred()) throw Raised{};
+  if (eq != 1) {
+    PyErr_Format(PyExc_ValueError, "%s must be an integer, got %R", name, o);
+    throw Raised{};
+  }
   return v;
 }
 
@@ -111,24 +114,25 @@ int32_t integer32(PyObject* o) {
   return v;
 }
 
-// o == 4 or o == 8, by value.
-int32_t bits_4_or_8(PyObject* o) {
-  if (!PyLong_CheckExact(o)) {
-    for (const int32_t v : {4, 8}) {
-      PyObject* n = PyLong_FromLong(v);
-      const int eq = n ? PyObject_RichCompareBool(o, n, Py_EQ) : -1;
-      Py_XDECREF(n);
-      if (eq < 0) throw Raised{};
-      if (eq) return v;
-    }
-    fail(PyExc_ValueError, "bits must be 4 or 8");
-  }
-  const int64_t v = integer(o);
-  if (v != 4 && v != 8) fail(PyExc_ValueError, "bits must be 4 or 8");
-  return (int32_t)v;
+// o == v, by value.
+bool equals(PyObject* o, long v) {
+  PyObject* n = PyLong_FromLong(v);
+  const int eq = n ? PyObject_RichCompareBool(o, n, Py_EQ) : -1;
+  Py_XDECREF(n);
+  if (eq < 0) throw Raised{};
+  return eq == 1;
 }
 
+int32_t bits_4_or_8(PyObject* o) {
+  if (equals(o, 4)) return 4;
+  if (equals(o, 8)) return 8;
+  fail(PyExc_ValueError, "bits must be 4 or 8");
+}
+
+// Codes of the entry points that leave the check of bits to the library: packed
+// where bits == 4, bytes for any other value.
 at::ScalarType code_dtype(int32_t bits) { return bits == 4 ? at::kByte : at::kChar; }
+int32_t code_bits(PyObject* bits) { return equals(bits, 4) ? 4 : 8; }
 
 // An output: the caller's tensor after its checks, or a new one.
 struct Out {
@@ -268,11 +272,11 @@ PyObject* rotate_quant_range(PyObject* const* a) {
   const at::Tensor& x = tensor(a[0], "x", at::kHalf);
   if (x.dim() != 2) fail(PyExc_ValueError, "x must be 2-D [M, K]");
   const int64_t M = x.size(0), K = x.size(1);
-  const int32_t bits = integer32(a[2]);
-  Out codes(a[3], "codes", code_dtype(bits), {M, bits == 4 ? K / 2 : K}, x);
+  const int32_t cb = code_bits(a[2]);
+  Out codes(a[3], "codes", code_dtype(cb), {M, cb == 4 ? K / 2 : K}, x);
   Out scales(a[4], "scales", at::kFloat, {M}, x);
   Out zeros(a[5], "zeros", at::kInt, {M}, x);
-  const int32_t h = integer32(a[1]);
+  const int32_t h = integer32(a[1]), bits = integer32(a[2]);
   call("dptq_rotate_quant_range", x, dptq_rotate_quant_range, ptr(x), M, K, h, bits, codes.ptr(),
        scales.ptr<float>(), zeros.ptr<int32_t>());
   return tuple(codes, scales, zeros);
@@ -343,7 +347,7 @@ PyObject* qlinear_decode_native(PyObject* const* a) {
 
 // qlinear_fp6(a6, a_scales, w6, w_scales, M, K, N, y)
 PyObject* qlinear_fp6(PyObject* const* a) {
-  const int64_t M = integer(a[4]), K = integer(a[5]), N = integer(a[6]);
+  const int64_t M = integer(a[4], "M"), K = integer(a[5], "K"), N = integer(a[6], "N");
   const at::Tensor& a6 = tensor_of(a[0], "a_fp6", at::kByte, {fp6_bytes(M, K)});
   const at::Tensor& w6 = tensor_of(a[2], "w_fp6", at::kByte, {fp6_bytes(N, K)});
   const at::Tensor& as = tensor_of(a[1], "a_scales", at::kFloat, {M});
@@ -363,11 +367,11 @@ PyObject* qlinear_decode_fused(PyObject* const* a) {
   const int64_t N = dim(THPVariable_Unpack(a[3]), 0);
   const at::Tensor& w = tensor_of(a[3], "w_packed", at::kByte, {N, K / 2});
   const at::Tensor& ws = tensor_of(a[4], "w_scales", at::kFloat, {N});
-  const int32_t bits = integer32(a[2]);
+  const int32_t cb = code_bits(a[2]);
   Out y(a[5], "y", at::kHalf, {M, N}, x);
-  Out codes(a[6], "codes", code_dtype(bits), {M, bits == 4 ? K / 2 : K}, x);
+  Out codes(a[6], "codes", code_dtype(cb), {M, cb == 4 ? K / 2 : K}, x);
   Out scales(a[7], "scales", at::kFloat, {M}, x);
-  const int32_t h = integer32(a[1]), mode = integer32(a[8]);
+  const int32_t h = integer32(a[1]), bits = integer32(a[2]), mode = integer32(a[8]);
   call("dptq_qlinear_decode_fused", x, dptq_qlinear_decode_fused, ptr(x), M, K, h, bits, ptr<uint8_t>(w),
        ptr<float>(ws), N, y.ptr(), codes.ptr(), scales.ptr<float>(), mode);
   return tuple(y, codes, scales);
@@ -381,14 +385,15 @@ PyObject* qlinear_range(PyObject* const* a) {
   const at::Tensor& wt = THPVariable_Unpack(a[4]);
   if (wt.dim() != 2) fail(PyExc_ValueError, "w_packed must be 2-D [N, K/2]");
   const int64_t N = wt.size(0), K = 2 * wt.size(1);
-  const int32_t bits = integer32(a[3]);
-  const at::Tensor& codes = tensor_of(a[0], "codes", code_dtype(bits), {M, bits == 4 ? K / 2 : K});
+  const int32_t cb = code_bits(a[3]);
+  const at::Tensor& codes = tensor_of(a[0], "codes", code_dtype(cb), {M, cb == 4 ? K / 2 : K});
   const at::Tensor& s = tensor_of(a[1], "scales", at::kFloat, {M});
   const at::Tensor& z = tensor_of(a[2], "zeros", at::kInt, {M});
   const at::Tensor& w = tensor_of(a[4], "w_packed", at::kByte, {N, K / 2});
   const at::Tensor& ws = tensor_of(a[5], "w_scales", at::kFloat, {N});
   const at::Tensor& sums = tensor_of(a[6], "w_sums", at::kInt, {N});
   Out y(a[7], "y", at::kHalf, {M, N}, codes);
+  const int32_t bits = integer32(a[3]);
   call("dptq_qlinear_range", codes, dptq_qlinear_range, ptr(codes), ptr<float>(s), ptr<int32_t>(z), M, K,
        bits, ptr<uint8_t>(w), ptr<float>(ws), ptr<int32_t>(sums), N, y.ptr());
   return y.release();
@@ -405,8 +410,10 @@ PyObject* residual_dynamics(PyObject* const* a) {
   Out snr(a[6], "snr", at::kFloat, {T}, x);
   Out means(a[7], "means", at::kDouble, {2}, x);
   const int32_t h = integer32(a[2]);
-  const double eps = PyFloat_AsDouble(a[4]);
-  if (eps == -1.0 && PyErr_Occurred()) throw Raised{};
+  PyObject* f = PyNumber_Float(a[4]);
+  if (!f) throw Raised{};
+  const double eps = PyFloat_AS_DOUBLE(f);
+  Py_DECREF(f);
   call("dptq_residual_dynamics", x, dptq_residual_dynamics, ptr(x), ptr(dx), T, K, h, bits, (float)eps,
        jr.ptr<float>(), snr.ptr<float>(), means.ptr<double>());
   return tuple(jr, snr, means);
@@ -416,8 +423,9 @@ PyObject* residual_dynamics(PyObject* const* a) {
 PyObject* kv_quant(PyObject* const* a) {
   const at::Tensor& kv = tensor(a[0], "kv", at::kHalf);
   two_d(kv, "kv must be 2-D [T, D]");
-  const int64_t T = kv.size(0), D = kv.size(1), group = integer(a[1]);
+  const int64_t T = kv.size(0), D = kv.size(1), group = integer(a[1], "group", true);
   if (group <= 0 || D % group) fail(PyExc_ValueError, "D must be a multiple of group");
+  if (a[3] == Py_None || a[4] == Py_None) integer(a[1], "group");   // sizes the new buffers
   Out codes(a[2], "codes", at::kByte, {T, D / 2}, kv);
   Out scales(a[3], "scales", at::kFloat, {T, D / group}, kv);
   Out mins(a[4], "mins", at::kFloat, {T, D / group}, kv);
@@ -431,7 +439,7 @@ PyObject* kv_quant(PyObject* const* a) {
 PyObject* kv_dequant(PyObject* const* a) {
   const at::Tensor& codes = tensor(a[0], "codes", at::kByte);
   two_d(codes, "codes must be 2-D [T, D/2]");
-  const int64_t T = codes.size(0), D = 2 * codes.size(1), group = integer(a[3]);
+  const int64_t T = codes.size(0), D = 2 * codes.size(1), group = integer(a[3], "group", true);
   if (group <= 0 || D % group) fail(PyExc_ValueError, "D must be a multiple of group");
   const at::Tensor& scales = tensor_of(a[1], "scales", at::kFloat, {T, D / group});
   const at::Tensor& mins = tensor_of(a[2], "mins", at::kFloat, {T, D / group});

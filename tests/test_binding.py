@@ -65,6 +65,46 @@ def test_tensors_without_storage_raise():
     assert lines == ["Cannot access data pointer of Tensor that doesn't have storage"] * 9, r.stdout
 
 
+# Arguments that are no plain integers: what the checks refuse, and what reaches
+# the library (which refuses the null pointers of fake tensors: status 1).
+_NUMBERS = """
+import torch, numpy as np, paper_2606_12487_amd as dptq
+from torch._subclasses import FakeTensorMode
+dptq._binding().init(dptq._check, lambda device: 0)
+with FakeTensorMode():
+    empty = lambda dtype, *shape: torch.empty(shape, dtype=dtype, device="cuda")
+    x, s, w = empty(torch.float16, 3, 128), empty(torch.float32, 3), empty(torch.uint8, 16, 64)
+    c, c8, m = empty(torch.uint8, 3, 64), empty(torch.int8, 3, 128), empty(torch.float32, 3, 1)
+    ws, z, y, zw = empty(torch.float32, 16), empty(torch.int32, 3), empty(torch.float16, 3, 16), empty(torch.int32, 16)
+    a6, w6 = empty(torch.uint8, 3072), empty(torch.uint8, 3072)
+    for call in [
+        lambda: dptq.kv_quant(x, 128.5), lambda: dptq.kv_quant(x, "128"), lambda: dptq.kv_quant(x, 128.0),
+        lambda: dptq.kv_quant(x, 128.0, c, m, m), lambda: dptq.kv_quant(x, np.int64(128)),
+        lambda: dptq.kv_dequant(c, m, m, 128.5), lambda: dptq.kv_dequant(c, m, m, np.float32(128)),
+        lambda: dptq.qlinear_fp6(a6, s, w6, ws, 3.0, 128, 16, y),
+        lambda: dptq.qlinear_fp6(a6, s, w6, ws, 3, "128", 16, y),
+        lambda: dptq.qlinear_range(c, s, z, 4.5, w, ws, zw), lambda: dptq.qlinear_range(c8, s, z, 8.0, w, ws, zw),
+        lambda: dptq.rotate_quant_range(x, 128, 4.5, c), lambda: dptq.qlinear_decode_fused(x, 128, None, w, ws, y, c),
+        lambda: dptq.rotate_quant(x, 128, 2**70),
+        lambda: dptq.residual_dynamics(x, x, 128, 4, "1e-8"),
+    ]:
+        try:
+            call()
+            print("no error")
+        except Exception as e:
+            print(type(e).__name__, getattr(e, "status", ""))
+"""
+
+
+def test_numbers_accepted_and_refused():
+    r = subprocess.run([sys.executable, "-c", _NUMBERS], capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, (r.returncode, r.stdout, r.stderr[-2000:])
+    assert [line.strip() for line in r.stdout.splitlines()] == [
+        "ValueError", "TypeError", "TypeError", "DptqError 1", "DptqError 1", "ValueError", "DptqError 1",
+        "TypeError", "TypeError", "TypeError", "DptqError 1", "TypeError", "TypeError", "ValueError",
+        "DptqError 1"], r.stdout
+
+
 @pytest.mark.gpu
 def test_buffers_shapes_and_statuses():
     x = torch.randn(3, 256, device="cuda").half()
