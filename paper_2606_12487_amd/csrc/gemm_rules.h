@@ -1,0 +1,214 @@
+// Which GEMM kernel and tile a shape runs: pure functions of the sizes and the
+// compute units, evaluated once per call (host only, no HIP, so that they can be
+// checked without a GPU).  Estimates are in microseconds; the kernels that they
+// choose between return the same bits.
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+namespace dptq {
+
+// GEMM kernels (values of dptq_gemm_kernel, then kGemmKsplit: the K-split
+// kernel that serves kGemmDecode, for M > 16 on a tile the dispatch chose).
+constexpr int kGemmAuto = 0, kGemmDecode = 1, kGemmTile = 2, kGemmWide = 3, kGemmKsplit = 4;
+
+namespace rules {
+
+constexpr int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// A tile of a K-split kernel (-1: none) and its estimated time.
+struct TilePlan {
+  int tile;
+  double cost;
+};
+
+// ---------------------------------------------------------------------------
+// K-split int8 GEMM, M > 16.  Tiles (TI, TJ, the wavefronts that split K), and
+// the estimate of each: a start, then per round of `resident` workgroups a
+// compute unit a fixed part and the k loop, then what grows with every tile a
+// compute unit runs, with the weights' way from memory and with the output's.
+// Fitted to 288 shapes a bit width (M 20-1024, N 1024-28672, K 2048-28672;
+// weights cycling through 300 MB): the tile picked is within 2% of the best of
+// 20 on average.
+// ---------------------------------------------------------------------------
+struct KsplitTile {
+  int ti, tj, waves, resident;
+  double start, round, round_k, tile_k, kn, mn;
+};
+constexpr KsplitTile kKsplitTiles4[] = {
+    {1, 1, 8, 2, 2.38, 0.00, 9.85e-05, 1.08e-04, 2.16e-08, 2.90e-06},
+    {1, 2, 8, 1, 2.57, 0.00, 2.45e-04, 0.00e+00, 2.50e-08, 1.78e-06},
+    {2, 2, 8, 1, 2.52, 0.11, 3.35e-04, 0.00e+00, 2.93e-08, 1.51e-06},
+    {2, 3, 8, 1, 2.74, 0.27, 4.43e-04, 0.00e+00, 2.02e-08, 1.03e-06},
+    {2, 4, 8, 1, 1.79, 1.31, 5.76e-04, 0.00e+00, 1.70e-08, 1.07e-06},
+    {4, 3, 8, 1, 1.70, 1.83, 6.98e-04, 0.00e+00, 2.56e-08, 6.68e-07},
+    {2, 2, 4, 2, 2.75, 0.00, 3.36e-04, 1.77e-04, 2.87e-08, 5.92e-07},
+    {2, 3, 4, 3, 2.95, 0.00, 3.43e-04, 3.31e-04, 1.53e-08, 7.78e-07},
+    {2, 4, 4, 2, 3.02, 0.00, 4.13e-04, 3.16e-04, 1.81e-08, 9.85e-07},
+    {4, 4, 4, 2, 2.95, 0.86, 4.29e-04, 7.25e-04, 1.87e-08, 7.25e-07},
+    {8, 4, 4, 1, 1.68, 4.39, 1.57e-03, 0.00e+00, 1.81e-08, 4.62e-07},
+    {4, 8, 4, 1, 1.82, 3.80, 1.66e-03, 0.00e+00, 1.26e-08, 4.27e-07}};
+constexpr KsplitTile kKsplitTiles8[] = {
+    {1, 1, 8, 1, 2.40, 0.00, 2.27e-04, 0.00e+00, 2.72e-08, 2.63e-06},
+    {1, 2, 8, 1, 2.37, 0.00, 3.68e-04, 0.00e+00, 2.37e-08, 2.57e-06},
+    {2, 2, 8, 1, 1.72, 0.71, 4.71e-04, 0.00e+00, 2.46e-08, 2.37e-06},
+    {2, 3, 8, 1, 1.73, 0.97, 6.26e-04, 0.00e+00, 1.35e-08, 1.63e-06},
+    {4, 3, 8, 1, 1.53, 1.57, 8.43e-04, 0.00e+00, 2.26e-08, 9.59e-07},
+    {2, 4, 4, 1, 2.56, 0.00, 7.39e-04, 0.00e+00, 1.60e-08, 1.03e-06},
+    {4, 2, 4, 2, 2.36, 0.41, 1.03e-04, 5.87e-04, 2.77e-08, 8.12e-07},
+    {4, 4, 4, 1, 1.51, 2.06, 1.01e-03, 0.00e+00, 1.69e-08, 8.48e-07},
+    {4, 6, 4, 1, 1.58, 2.73, 1.32e-03, 0.00e+00, 1.21e-08, 8.05e-07},
+    {4, 8, 4, 1, 1.65, 3.53, 1.63e-03, 0.00e+00, 1.82e-08, 6.65e-07},
+    {8, 4, 4, 1, 1.74, 3.79, 1.59e-03, 0.00e+00, 1.90e-08, 6.60e-07}};
+constexpr int ksplit_tiles(int bits) {
+  return bits == 4 ? sizeof(kKsplitTiles4) / sizeof(kKsplitTiles4[0])
+                   : sizeof(kKsplitTiles8) / sizeof(kKsplitTiles8[0]);
+}
+constexpr KsplitTile ksplit_tile(int bits, int i) { return bits == 4 ? kKsplitTiles4[i] : kKsplitTiles8[i]; }
+
+// The estimate of a tile of which the fullest compute unit runs q.
+template <class Tile>
+double ksplit_tile_us(const Tile& t, int64_t q, int64_t M, int64_t N, int K) {
+  const double rounds = (double)ceil_div(q, t.resident), k = (double)K;
+  return t.start + rounds * (t.round + k * t.round_k) + (double)q * k * t.tile_k + t.kn * k * (double)N +
+         t.mn * (double)M * (double)N;
+}
+
+// The tile with the lowest estimate among those that give a compute unit at most
+// three rounds (and at least six tiles), where the fitted shapes lie.
+inline TilePlan ksplit_plan(int64_t M, int64_t N, int K, int bits, int cus) {
+  TilePlan best{-1, 0.0};
+  for (int i = 0; i < ksplit_tiles(bits); ++i) {
+    const KsplitTile t = ksplit_tile(bits, i);
+    const int64_t q = ceil_div(ceil_div(M, 16 * t.tj) * ceil_div(N, 16 * t.ti), cus);
+    if (q > 3 * (t.resident > 2 ? t.resident : 2)) continue;
+    const double c = ksplit_tile_us(t, q, M, N, K);
+    if (best.tile < 0 || c < best.cost) best = {i, c};
+  }
+  return best;
+}
+
+// Output tiles (n x m) of the two int8 tile kernels; the wide one needs a full
+// tile and a ring's worth of k.
+constexpr int kTileN = 256, kTileM = 128, kWideN = 192, kWideM = 256;
+constexpr int wide_min_k(int bits) { return bits == 4 ? 512 : 384; }
+inline bool wide_fits(int64_t M, int64_t N, int K, int bits) {
+  return M >= kWideM && N >= kWideN && K >= wide_min_k(bits);
+}
+
+// Which of the two: relative time, rounds of one tile per compute unit times the
+// tile's area over the measured throughput of the tile shape (large prefill
+// shapes).
+constexpr double kWideSpeed = 1.3;
+inline double tile_launch_cost(int64_t M, int64_t N, int bm, int bn, double speed, int cus) {
+  return (double)ceil_div(ceil_div(M, bm) * ceil_div(N, bn), cus) * (double)bm * (double)bn / speed;
+}
+inline bool wide_is_faster(int64_t M, int64_t N, int K, int bits, int cus) {
+  return wide_fits(M, N, K, bits) && tile_launch_cost(M, N, kWideM, kWideN, kWideSpeed, cus) <=
+                                         tile_launch_cost(M, N, kTileM, kTileN, 1.0, cus);
+}
+
+// Estimate of a 256 x 128 or 192 x 256 tile kernel: a start, then per round of
+// one tile per compute unit its k loop (slower when every unit is busy: power)
+// and its epilogue.  Fitted to measured times over M 17-1024, N 1024-28672, K
+// 2048-14336, within 4%.
+inline double tile_kernel_us(int64_t M, int64_t N, int K, int bits, bool wide, int cus) {
+  const int64_t bm = wide ? kWideM : kTileM, bn = wide ? kWideN : kTileN;
+  const int64_t tiles = ceil_div(M, bm) * ceil_div(N, bn);
+  const double rounds = (double)ceil_div(tiles, cus), k = (double)K;
+  const double fill = tiles < cus ? (double)tiles / cus : 1.0;
+  if (bits == 4)
+    return wide ? 3.0 + rounds * (5.85 + k * (5.81e-3 + 1.43e-3 * fill))
+                : 1.8 + rounds * (4.35 + k * (5.12e-3 + 0.87e-3 * fill));
+  return wide ? 3.9 + rounds * (5.0 + k * (5.55e-3 + 2.17e-3 * fill))
+              : 1.4 + rounds * (4.76 + k * (4.59e-3 + 1.45e-3 * fill));
+}
+
+// The kernel of a shape, and the K-split kernel's tile.  M <= 16 streams the
+// weights; otherwise the K-split kernel where its estimate is at least 8% below
+// the tile kernels' (it is the less exact).  At K = 14336, N = 4096, 4 bits it
+// takes 8.7 us against 83 us at M = 48, 18.6 against 80 at M = 256, 31.6 against
+// 80.5 at M = 512, 64.8 against 83 at M = 1024; at K = 2048, N = 11008 it stops
+// paying at M = 384 (17.1 against 17.9 us).
+struct GemmRoute {
+  int kernel, tile;
+};
+inline GemmRoute gemm_route(int64_t M, int64_t N, int K, int bits, int cus) {
+  if (M <= 16) return {kGemmDecode, -1};
+  const bool wide = wide_is_faster(M, N, K, bits, cus);
+  const TilePlan p = ksplit_plan(M, N, K, bits, cus);
+  if (p.tile >= 0 && 1.08 * p.cost < tile_kernel_us(M, N, K, bits, wide, cus)) return {kGemmKsplit, p.tile};
+  return {wide ? kGemmWide : kGemmTile, -1};
+}
+
+// Workgroup of the K-split kernel for at most 16 tokens, as blocks of 16 channels
+// and wavefronts: one block while these fit the compute units (about) once, two
+// on eight wavefronts while those do, then two on four wavefronts (several
+// workgroups per compute unit keep the loads going) up to four blocks per
+// compute unit, and two on eight beyond.  Measured at M = 8, 4 bits, canonical
+// weights: N = 4096, K = 4096: 3.71 us against 3.92 and 4.6 us for the other
+// two; N = 8192, K = 8192: 8.0-8.3 us for eight wavefronts against 9.6; N =
+// 10240, K = 8192: 10.7, 11.3 and 10.0 us; N = 57344, K = 8192: 46, 41.4 and
+// 42.4 us.
+struct DecodeTile {
+  int ti, waves;
+};
+inline DecodeTile decode_tile(int64_t N, int cus) {
+  const int64_t nb = N / 16;
+  if (8 * nb <= 9 * (int64_t)cus) return {1, 8};
+  if (nb > 2 * (int64_t)cus && nb <= 4 * (int64_t)cus) return {2, 4};
+  return {2, 8};
+}
+
+// ---------------------------------------------------------------------------
+// K-split FP6 GEMM.  Tiles as above in blocks of 32, with the stages a wavefront
+// keeps.  Fitted to 217 shapes (M 64-2048, N 1024-28672, K 2048-28672; weights
+// cycling through 300 MB): the estimate is within 10% (one standard deviation),
+// and the tile that it picks within 0.3% of the best one on average, 15% at
+// worst.
+// ---------------------------------------------------------------------------
+struct Fp6KsplitTile {
+  int ti, tj, waves, bufs, resident;
+  double start, round, round_k, tile_k, kn, mn;
+};
+constexpr Fp6KsplitTile kFp6KsplitTiles[] = {
+    {1, 1, 8, 2, 1, 1.33, 0.62, 5.14e-4, 0.0, 2.26e-8, 2.32e-6},
+    {1, 2, 8, 2, 1, 1.43, 0.82, 7.42e-4, 0.0, 3.37e-8, 1.57e-6},
+    {2, 2, 4, 1, 3, 3.09, 0.23, 1.92e-4, 8.91e-4, 4.00e-8, 5.79e-7},
+    {2, 2, 4, 2, 1, 1.72, 0.91, 1.00e-3, 0.0, 3.93e-8, 1.21e-6},
+    {2, 3, 4, 2, 1, 1.65, 1.67, 1.21e-3, 0.0, 2.98e-8, 1.06e-6},
+    {2, 4, 4, 2, 1, 1.91, 2.03, 1.47e-3, 0.0, 3.17e-8, 1.07e-6},
+    {4, 3, 4, 1, 1, 2.16, 3.48, 1.70e-3, 0.0, 3.89e-8, 9.07e-7},
+    {4, 4, 4, 1, 1, 1.83, 4.98, 1.99e-3, 0.0, 4.41e-8, 7.70e-7}};
+constexpr int kNumFp6KsplitTiles = sizeof(kFp6KsplitTiles) / sizeof(kFp6KsplitTiles[0]);
+
+// The tile with the lowest estimate; those that run more than three rounds lie
+// beyond the fitted shapes and count only with any_size.
+inline TilePlan fp6_ksplit_plan(int64_t M, int64_t N, int K, bool any_size, int cus) {
+  TilePlan best{-1, 0.0};
+  for (int i = 0; i < kNumFp6KsplitTiles; ++i) {
+    const Fp6KsplitTile& t = kFp6KsplitTiles[i];
+    const int64_t q = ceil_div(ceil_div(ceil_div(M, 32), t.tj) * ceil_div(ceil_div(N, 32), t.ti), cus);
+    if (!any_size && q > 3 * t.resident) continue;
+    const double c = ksplit_tile_us(t, q, M, N, K);
+    if (best.tile < 0 || c < best.cost) best = {i, c};
+  }
+  return best;
+}
+
+// The K-split kernel's tile, or -1 for the 192 x 256 kernel.  That kernel takes
+// at least one full tile of padded rows each way and three stages per tile; of
+// those shapes it runs the ones whose estimate (whole rounds of its tiles, 6.9
+// us + 4.0 ns per k each, and the operands' and the output's way) the K-split
+// kernel's is not at least 5% below.
+inline int fp6_ksplit_or_none(int64_t M, int64_t N, int K, int cus) {
+  const bool fits = ceil_div(M, 32) >= 8 && ceil_div(N, 32) >= 6 && K >= 3 * 128;
+  const double rounds = (double)ceil_div(ceil_div(M, 256) * ceil_div(N, 192), cus), k = (double)K, n = (double)N;
+  const double cost = rounds * (6.91 + 3.99e-3 * k) + 5.98e-8 * k * n + 1.84e-7 * (double)M * n;
+  const TilePlan p = fp6_ksplit_plan(M, N, K, !fits, cus);
+  return p.tile >= 0 && (!fits || p.cost < 0.95 * cost) ? p.tile : -1;
+}
+
+}  // namespace rules
+}  // namespace dptq

@@ -5,6 +5,8 @@
 #include <hip/hip_fp16.h>
 #include <stdint.h>
 
+#include "gemm_rules.h"
+
 namespace dptq {
 
 // Hadamard size h = f * 2^j with f in {1, 28}.
@@ -47,10 +49,6 @@ hipError_t launch_kv_quant(const void* kv, int64_t T, int64_t D, int group, uint
 hipError_t launch_kv_dequant(const uint8_t* codes, const float* scales, const float* mins,
                              int64_t T, int64_t D, int group, void* out, hipStream_t stream);
 
-// GEMM kernels (values of dptq_gemm_kernel, then kGemmKsplit: the K-split
-// kernel that serves kGemmDecode, at any M).
-constexpr int kGemmAuto = 0, kGemmDecode = 1, kGemmTile = 2, kGemmWide = 3, kGemmKsplit = 4;
-
 // One call of the K-split GEMM (qgemm_ksplit.hip): y from the dequant epilogue,
 // with the zero-point correction when a_zeros is given, or the raw
 // accumulators when acc is.
@@ -70,9 +68,8 @@ struct KsplitCall {
 // Weight layouts: canonical nibbles (any output), the 8-bit activation order
 // (bits 8, y), the decode layout (M <= 16, y or acc).
 constexpr int kWeightsCanonical = 0, kWeightsA8Order = 2, kWeightsDecode = 3;
-hipError_t launch_ksplit(const KsplitCall& c, int bits, int weights, hipStream_t stream);
-// Estimated microseconds of its best tile for M > 16.
-double ksplit_cost(int64_t M, int64_t N, int K, int bits);
+// tile: for M > 16, the tile of gemm_rules.h that the dispatch chose.
+hipError_t launch_ksplit(const KsplitCall& c, int bits, int weights, int tile, hipStream_t stream);
 
 // Whether a kernel covers the shape (kGemmAuto and kGemmTile cover all).
 bool gemm_kernel_fits(int kernel, int64_t M, int64_t N, int K, int bits);
@@ -152,14 +149,7 @@ hipError_t launch_pack_fp6(const uint8_t* codes, int64_t R, int K, uint8_t* out,
 hipError_t launch_qlinear_fp6(const uint8_t* a6, const float* a_scales, int64_t M, int K,
                               const uint8_t* w6, const float* w_scales, int64_t N, void* y,
                               int32_t* out_acc, hipStream_t stream);
-// Its kernel for medium batches (qgemm_fp6_ksplit.hip): the best tile and its
-// estimated microseconds (tile -1: none in the range of the estimates, unless
-// any_size), and one launch of it.
-struct Fp6KsplitPlan {
-  int tile;
-  double cost;
-};
-Fp6KsplitPlan fp6_ksplit_plan(int64_t M, int64_t N, int K, bool any_size);
+// Its kernel for medium batches (qgemm_fp6_ksplit.hip), on a tile of gemm_rules.h.
 hipError_t launch_fp6_ksplit(int tile, const uint8_t* a6, const float* a_scales, int64_t M, int K,
                              const uint8_t* w6, const float* w_scales, int64_t N, void* y, int32_t* acc,
                              hipStream_t stream);

@@ -946,57 +946,11 @@ void launch_wide(const uint8_t* a, const float* as, int64_t M, int K, const uint
                      0, stream, a, as, w, ws, (int)M, (int)N, K, y, acc, az, wsum);
 }
 
-// Relative time of a launch: rounds of one tile per compute unit, times the
-// tile's area over the measured throughput of the tile shape.
-double launch_cost(int64_t M, int64_t N, int bm, int bn, double speed, int cus) {
-  const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-  return (double)((tiles + cus - 1) / cus) * (double)bm * (double)bn / speed;
-}
-
-// Throughput of the wide tiles per unit of tile area relative to the
-// 256 x 128 tiles (measured on large prefill shapes).
-constexpr double kWideSpeed = 1.3;
-
-template <int BITS>
-bool wide_fits(int64_t M, int64_t N, int K) {
-  using W = Wide<BITS>;
-  return M >= W::kBM && N >= W::kBN && K >= W::kMinK;
-}
-
-// Estimated microseconds of a tile kernel: a start, then per round of one tile
-// per compute unit its k loop (slower when every unit is busy: power) and its
-// epilogue.  Fitted to measured times over M 17-1024, N 1024-28672, K
-// 2048-14336, within 4%.
-double tile_kernel_us(int64_t M, int64_t N, int K, int bits, bool wide, int cus) {
-  const int64_t bm = wide ? 256 : 128, bn = wide ? 192 : 256;
-  const int64_t tiles = ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-  const double rounds = (double)((tiles + cus - 1) / cus), k = (double)K;
-  const double fill = tiles < cus ? (double)tiles / cus : 1.0;
-  if (bits == 4)
-    return wide ? 3.0 + rounds * (5.85 + k * (5.81e-3 + 1.43e-3 * fill))
-                : 1.8 + rounds * (4.35 + k * (5.12e-3 + 0.87e-3 * fill));
-  return wide ? 3.9 + rounds * (5.0 + k * (5.55e-3 + 2.17e-3 * fill))
-              : 1.4 + rounds * (4.76 + k * (4.59e-3 + 1.45e-3 * fill));
-}
-
-// Kernel for a shape: M <= 16 streams the weights; otherwise the tile shape
-// with the smaller estimated time (the wide tiles need at least one full
-// tile and a ring's worth of k), or the K-split kernel where that is estimated
-// at least 8% faster still (its estimate is the less exact).  At K = 14336,
-// N = 4096, 4 bits it takes 8.7 us against 83 us at M = 48, 18.6 against
-// 80 at M = 256, 31.6 against 80.5 at M = 512, 64.8 against 83 at M = 1024; at
-// K = 2048, N = 11008 it stops paying at M = 384 (17.1 against 17.9 us).
-template <int BITS>
-int auto_kernel(int64_t M, int64_t N, int K) {
-  if (M <= 16) return kGemmDecode;
-  using S = PrefillCfg<BITS>;
-  using W = Wide<BITS>;
-  const int cus = device_cus();
-  const bool wide = wide_fits<BITS>(M, N, K) && launch_cost(M, N, W::kBM, W::kBN, kWideSpeed, cus) <=
-                                                    launch_cost(M, N, S::kBM, S::kBN, 1.0, cus);
-  if (1.08 * ksplit_cost(M, N, K, BITS) < tile_kernel_us(M, N, K, BITS, wide, cus)) return kGemmKsplit;
-  return wide ? kGemmWide : kGemmTile;
-}
+static_assert(Wide<4>::kMinK == rules::wide_min_k(4) && Wide<8>::kMinK == rules::wide_min_k(8) &&
+                  Wide<4>::kBM == rules::kWideM && Wide<4>::kBN == rules::kWideN &&
+                  PrefillCfg<4>::kBM == rules::kTileM && PrefillCfg<4>::kBN == rules::kTileN &&
+                  PrefillCfg<8>::kBM == rules::kTileM && PrefillCfg<8>::kBN == rules::kTileN,
+              "the dispatch rules are for these tiles");
 
 template <int BITS, bool ACC_OUT, bool WA8 = false, bool ZP = false>
 hipError_t launch_t(const uint8_t* a, const float* as, int64_t M, int K,
@@ -1004,15 +958,16 @@ hipError_t launch_t(const uint8_t* a, const float* as, int64_t M, int K,
                     int32_t* acc, int kernel, hipStream_t stream,
                     const int32_t* az = nullptr, const int32_t* wsum = nullptr) {
   if (M == 0) return hipSuccess;
-  if (kernel == kGemmAuto) kernel = auto_kernel<BITS>(M, N, K);
-  switch (kernel) {
+  const int cus = device_cus();
+  const rules::GemmRoute c = kernel == kGemmAuto ? rules::gemm_route(M, N, K, BITS, cus) : rules::GemmRoute{kernel, -1};
+  switch (c.kernel) {
     case kGemmDecode:
     case kGemmKsplit:
       return launch_ksplit(KsplitCall{a, as, M, K, w, ws, N, ACC_OUT ? nullptr : y, ACC_OUT ? acc : nullptr,
                                       az, wsum},
-                           BITS, WA8 ? kWeightsA8Order : kWeightsCanonical, stream);
+                           BITS, WA8 ? kWeightsA8Order : kWeightsCanonical, c.tile, stream);
     case kGemmWide:
-      launch_wide<BITS, ACC_OUT, WA8, ZP>(a, as, M, K, w, ws, N, y, acc, az, wsum, device_cus(), stream);
+      launch_wide<BITS, ACC_OUT, WA8, ZP>(a, as, M, K, w, ws, N, y, acc, az, wsum, cus, stream);
       break;
     default:
       launch_prefill<PrefillCfg<BITS>, ACC_OUT, WA8, ZP>(a, as, M, K, w, ws, N, y, acc, az, wsum, stream);
@@ -1045,7 +1000,7 @@ bool gemm_kernel_fits(int kernel, int64_t M, int64_t N, int K, int bits) {
     case kGemmDecode:
       return M <= 16;
     case kGemmWide:
-      return bits == 4 ? wide_fits<4>(M, N, K) : wide_fits<8>(M, N, K);
+      return rules::wide_fits(M, N, K, bits);
     default:
       return false;
   }
@@ -1103,7 +1058,7 @@ hipError_t launch_qlinear_decode_native(const void* codes, const float* a_scales
                                         int64_t N, void* y, int32_t* out_acc, hipStream_t stream) {
   return launch_ksplit(KsplitCall{static_cast<const uint8_t*>(codes), a_scales, M, K, w_dec, w_scales, N,
                                   static_cast<__half*>(y), out_acc, nullptr, nullptr},
-                       bits, kWeightsDecode, stream);
+                       bits, kWeightsDecode, -1, stream);
 }
 
 hipError_t launch_qlinear_a8(const void* codes, const float* a_scales, int64_t M, int K,

@@ -511,19 +511,10 @@ hipError_t launch_qlinear_fp6(const uint8_t* a6, const float* a_scales, int64_t 
                               const uint8_t* w6, const float* w_scales, int64_t N, void* y,
                               int32_t* out_acc, hipStream_t stream) {
   if (M == 0) return hipSuccess;
-  // This kernel takes at least one full tile of padded rows each way and
-  // three stages per tile; of those shapes it runs the ones whose estimated
-  // microseconds are not above the K-split kernel's by 5% or more (whole rounds of
-  // 192 x 256 tiles, 6.9 us + 4.0 ns per k each, and the operands' and the
-  // output's way; fitted like the K-split kernel's tiles).
+  const int cus = device_cus(), tile = rules::fp6_ksplit_or_none(M, N, K, cus);
+  if (tile >= 0) return launch_fp6_ksplit(tile, a6, a_scales, M, K, w6, w_scales, N, y, out_acc, stream);
   const int64_t tiles = ((M + F6::kBM - 1) / F6::kBM) * ((N + F6::kBN - 1) / F6::kBN);
-  const int64_t cus = device_cus(), grid = tiles < cus ? tiles : cus;
-  const bool fits = (M + 31) / 32 >= F6::kABlk && (N + 31) / 32 >= F6::kWBlk && K >= 3 * 128;
-  const double rounds = (double)((tiles + cus - 1) / cus), k = (double)K, n = (double)N;
-  const double cost = rounds * (6.91 + 3.99e-3 * k) + 5.98e-8 * k * n + 1.84e-7 * (double)M * n;
-  const Fp6KsplitPlan plan = fp6_ksplit_plan(M, N, K, !fits);
-  if (plan.tile >= 0 && (!fits || plan.cost < 0.95 * cost))
-    return launch_fp6_ksplit(plan.tile, a6, a_scales, M, K, w6, w_scales, N, y, out_acc, stream);
+  const int64_t grid = tiles < cus ? tiles : cus;
   __half* yh = static_cast<__half*>(y);
   if (out_acc)
     hipLaunchKernelGGL((qgemm_fp6<true>), dim3((unsigned)grid), dim3(256), 0, stream, a6, a_scales, w6,

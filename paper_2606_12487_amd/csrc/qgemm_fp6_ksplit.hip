@@ -186,50 +186,15 @@ qgemm_fp6_ksplit(const uint8_t* __restrict__ a6, const float* __restrict__ a_sca
   }
 }
 
-// Tiles, and the estimated microseconds of each: a start, then per round of
-// `resident` workgroups a compute unit a fixed part and the k loop, then what
-// grows with every tile a compute unit runs, with the weights' way from memory
-// and with the output's.  Fitted to 217 shapes (M 64-2048, N 1024-28672,
-// K 2048-28672; weights cycling through 300 MB): the estimate is within 10%
-// (one standard deviation), and the tile that it picks within 0.3% of the best
-// one on average, 15% at worst.
-struct Tile {
-  int ti, tj, waves, bufs, resident;
-  double start, round, round_k, tile_k, kn, mn;
-};
-constexpr Tile kTiles[] = {
-    {1, 1, 8, 2, 1, 1.33, 0.62, 5.14e-4, 0.0, 2.26e-8, 2.32e-6},
-    {1, 2, 8, 2, 1, 1.43, 0.82, 7.42e-4, 0.0, 3.37e-8, 1.57e-6},
-    {2, 2, 4, 1, 3, 3.09, 0.23, 1.92e-4, 8.91e-4, 4.00e-8, 5.79e-7},
-    {2, 2, 4, 2, 1, 1.72, 0.91, 1.00e-3, 0.0, 3.93e-8, 1.21e-6},
-    {2, 3, 4, 2, 1, 1.65, 1.67, 1.21e-3, 0.0, 2.98e-8, 1.06e-6},
-    {2, 4, 4, 2, 1, 1.91, 2.03, 1.47e-3, 0.0, 3.17e-8, 1.07e-6},
-    {4, 3, 4, 1, 1, 2.16, 3.48, 1.70e-3, 0.0, 3.89e-8, 9.07e-7},
-    {4, 4, 4, 1, 1, 1.83, 4.98, 1.99e-3, 0.0, 4.41e-8, 7.70e-7}};
-constexpr int kNumTiles = sizeof(kTiles) / sizeof(kTiles[0]);
-
-// Tiles the fullest compute unit runs.
-int64_t tiles_per_cu(const Tile& t, int64_t M, int64_t N) {
-  const int64_t mblk = (M + 31) / 32, nblk = (N + 31) / 32, cus = device_cus();
-  return (((mblk + t.tj - 1) / t.tj) * ((nblk + t.ti - 1) / t.ti) + cus - 1) / cus;
-}
-
-double tile_cost(const Tile& t, int64_t M, int64_t N, int K) {
-  const int64_t q = tiles_per_cu(t, M, N);
-  const double rounds = (double)((q + t.resident - 1) / t.resident), k = (double)K;
-  return t.start + rounds * (t.round + k * t.round_k) + (double)q * k * t.tile_k + t.kn * k * (double)N +
-         t.mn * (double)M * (double)N;
-}
-
 template <bool ACC_OUT, int I = 0>
 void launch_tile(int tile, const uint8_t* a6, const float* a_scales, int64_t M, int K, const uint8_t* w6,
                  const float* w_scales, int64_t N, __half* y, int32_t* acc, hipStream_t stream) {
-  if constexpr (I < kNumTiles) {
+  if constexpr (I < rules::kNumFp6KsplitTiles) {
     if (tile != I) {
       launch_tile<ACC_OUT, I + 1>(tile, a6, a_scales, M, K, w6, w_scales, N, y, acc, stream);
       return;
     }
-    constexpr Tile t = kTiles[I];
+    constexpr rules::Fp6KsplitTile t = rules::kFp6KsplitTiles[I];
     const int64_t mblk = (M + 31) / 32, nblk = (N + 31) / 32;
     const int64_t grid = ((mblk + t.tj - 1) / t.tj) * ((nblk + t.ti - 1) / t.ti);
     hipLaunchKernelGGL((qgemm_fp6_ksplit<t.ti, t.tj, t.waves, t.bufs, ACC_OUT>), dim3((unsigned)grid),
@@ -238,20 +203,6 @@ void launch_tile(int tile, const uint8_t* a6, const float* a_scales, int64_t M, 
 }
 
 }  // namespace
-
-// The estimates hold up to three rounds, where the shapes they were fitted to
-// lie; tiles beyond that count only for shapes the 192 x 256 kernel does not
-// take (any_size).
-Fp6KsplitPlan fp6_ksplit_plan(int64_t M, int64_t N, int K, bool any_size) {
-  Fp6KsplitPlan best{-1, 0.0};
-  for (int i = 0; i < kNumTiles; ++i) {
-    const Tile& t = kTiles[i];
-    if (!any_size && tiles_per_cu(t, M, N) > 3 * t.resident) continue;
-    const double c = tile_cost(t, M, N, K);
-    if (best.tile < 0 || c < best.cost) best = {i, c};
-  }
-  return best;
-}
 
 hipError_t launch_fp6_ksplit(int tile, const uint8_t* a6, const float* a_scales, int64_t M, int K,
                              const uint8_t* w6, const float* w_scales, int64_t N, void* y, int32_t* acc,

@@ -20,8 +20,6 @@
 // 27.5 us, 17.0 us and 13.8 us for the three, against 75 us for the 256 x 128
 // tile kernel on its 16 workgroups.
 
-#include <math.h>
-
 #include <type_traits>
 
 #include "internal.h"
@@ -388,51 +386,10 @@ void launch_cfg(const KsplitCall& c, hipStream_t stream) {
                      c.y, c.acc, c.a_zeros, c.w_sums);
 }
 
-// Tiles for M > 16 (TI, TJ, the wavefronts that split K), and the estimated
-// microseconds of each: a start, then per round of `resident` workgroups a
-// compute unit a fixed part and the k loop, then what grows with every tile a
-// compute unit runs, with the weights' way from memory and with the output's.
-// Fitted to 288 shapes a bit width (M 20-1024, N 1024-28672, K 2048-28672;
-// weights cycling through 300 MB): the tile picked is within 2% of the best of
-// 20 on average.
-struct Tile {
-  int ti, tj, waves, resident;
-  double start, round, round_k, tile_k, kn, mn;
-};
-constexpr Tile kTiles4[] = {
-    {1, 1, 8, 2, 2.38, 0.00, 9.85e-05, 1.08e-04, 2.16e-08, 2.90e-06},
-    {1, 2, 8, 1, 2.57, 0.00, 2.45e-04, 0.00e+00, 2.50e-08, 1.78e-06},
-    {2, 2, 8, 1, 2.52, 0.11, 3.35e-04, 0.00e+00, 2.93e-08, 1.51e-06},
-    {2, 3, 8, 1, 2.74, 0.27, 4.43e-04, 0.00e+00, 2.02e-08, 1.03e-06},
-    {2, 4, 8, 1, 1.79, 1.31, 5.76e-04, 0.00e+00, 1.70e-08, 1.07e-06},
-    {4, 3, 8, 1, 1.70, 1.83, 6.98e-04, 0.00e+00, 2.56e-08, 6.68e-07},
-    {2, 2, 4, 2, 2.75, 0.00, 3.36e-04, 1.77e-04, 2.87e-08, 5.92e-07},
-    {2, 3, 4, 3, 2.95, 0.00, 3.43e-04, 3.31e-04, 1.53e-08, 7.78e-07},
-    {2, 4, 4, 2, 3.02, 0.00, 4.13e-04, 3.16e-04, 1.81e-08, 9.85e-07},
-    {4, 4, 4, 2, 2.95, 0.86, 4.29e-04, 7.25e-04, 1.87e-08, 7.25e-07},
-    {8, 4, 4, 1, 1.68, 4.39, 1.57e-03, 0.00e+00, 1.81e-08, 4.62e-07},
-    {4, 8, 4, 1, 1.82, 3.80, 1.66e-03, 0.00e+00, 1.26e-08, 4.27e-07}};
-constexpr Tile kTiles8[] = {
-    {1, 1, 8, 1, 2.40, 0.00, 2.27e-04, 0.00e+00, 2.72e-08, 2.63e-06},
-    {1, 2, 8, 1, 2.37, 0.00, 3.68e-04, 0.00e+00, 2.37e-08, 2.57e-06},
-    {2, 2, 8, 1, 1.72, 0.71, 4.71e-04, 0.00e+00, 2.46e-08, 2.37e-06},
-    {2, 3, 8, 1, 1.73, 0.97, 6.26e-04, 0.00e+00, 1.35e-08, 1.63e-06},
-    {4, 3, 8, 1, 1.53, 1.57, 8.43e-04, 0.00e+00, 2.26e-08, 9.59e-07},
-    {2, 4, 4, 1, 2.56, 0.00, 7.39e-04, 0.00e+00, 1.60e-08, 1.03e-06},
-    {4, 2, 4, 2, 2.36, 0.41, 1.03e-04, 5.87e-04, 2.77e-08, 8.12e-07},
-    {4, 4, 4, 1, 1.51, 2.06, 1.01e-03, 0.00e+00, 1.69e-08, 8.48e-07},
-    {4, 6, 4, 1, 1.58, 2.73, 1.32e-03, 0.00e+00, 1.21e-08, 8.05e-07},
-    {4, 8, 4, 1, 1.65, 3.53, 1.63e-03, 0.00e+00, 1.82e-08, 6.65e-07},
-    {8, 4, 4, 1, 1.74, 3.79, 1.59e-03, 0.00e+00, 1.90e-08, 6.60e-07}};
-constexpr int num_tiles(int bits) {
-  return bits == 4 ? sizeof(kTiles4) / sizeof(kTiles4[0]) : sizeof(kTiles8) / sizeof(kTiles8[0]);
-}
-constexpr Tile tile_at(int bits, int i) { return bits == 4 ? kTiles4[i] : kTiles8[i]; }
-
 template <int BITS, bool ACC_OUT, bool WA8, bool ZP, int I = 0>
 void launch_tile(int tile, const KsplitCall& c, hipStream_t stream) {
-  if constexpr (I < num_tiles(BITS)) {
-    constexpr Tile t = tile_at(BITS, I);
+  if constexpr (I < rules::ksplit_tiles(BITS)) {
+    constexpr rules::KsplitTile t = rules::ksplit_tile(BITS, I);
     if (tile == I)
       launch_cfg<BITS, t.ti, t.tj, t.waves, ACC_OUT, WA8, ZP, false>(c, stream);
     else
@@ -440,72 +397,25 @@ void launch_tile(int tile, const KsplitCall& c, hipStream_t stream) {
   }
 }
 
-// One row of 16 tokens: one block of 16 channels per workgroup while these fit
-// the compute units (about) once, two on eight wavefronts while those do, then
-// two on four wavefronts (several workgroups per compute unit keep the loads
-// going) up to four blocks per compute unit, and two on eight beyond.
-// Measured at M = 8, 4 bits, canonical weights: N = 4096, K = 4096: 3.71 us
-// against 3.92 and 4.6 us for the other two; N = 8192, K = 8192: 8.0-8.3 us
-// for eight wavefronts against 9.6; N = 10240, K = 8192: 10.7, 11.3 and
-// 10.0 us; N = 57344, K = 8192: 46, 41.4 and 42.4 us.
 template <int BITS, bool ACC_OUT, bool WA8, bool ZP, bool WDEC>
 void launch_decode(const KsplitCall& c, hipStream_t stream) {
-  const int64_t nb = c.N / 16, cus = device_cus();
-  if (8 * nb <= 9 * cus) launch_cfg<BITS, 1, 1, 8, ACC_OUT, WA8, ZP, WDEC>(c, stream);
-  else if (nb > 2 * cus && nb <= 4 * cus) launch_cfg<BITS, 2, 1, 4, ACC_OUT, WA8, ZP, WDEC>(c, stream);
+  const rules::DecodeTile t = rules::decode_tile(c.N, device_cus());
+  if (t.ti == 1) launch_cfg<BITS, 1, 1, 8, ACC_OUT, WA8, ZP, WDEC>(c, stream);
+  else if (t.waves == 4) launch_cfg<BITS, 2, 1, 4, ACC_OUT, WA8, ZP, WDEC>(c, stream);
   else launch_cfg<BITS, 2, 1, 8, ACC_OUT, WA8, ZP, WDEC>(c, stream);
 }
 
-// Tiles the fullest compute unit runs.
-int64_t tiles_per_cu(const Tile& t, int64_t M, int64_t N) {
-  const int64_t cus = device_cus();
-  return (((M + 16 * t.tj - 1) / (16 * t.tj)) * ((N + 16 * t.ti - 1) / (16 * t.ti)) + cus - 1) / cus;
-}
-
-double tile_cost(const Tile& t, int64_t M, int64_t N, int K) {
-  const int64_t q = tiles_per_cu(t, M, N);
-  const double rounds = (double)((q + t.resident - 1) / t.resident), k = (double)K;
-  return t.start + rounds * (t.round + k * t.round_k) + (double)q * k * t.tile_k + t.kn * k * (double)N +
-         t.mn * (double)M * (double)N;
-}
-
-// The tile with the lowest estimate; in_range: among those that run at most
-// three rounds, where the fitted shapes lie (-1: none).
-int best_tile(int64_t M, int64_t N, int K, int bits, bool in_range, double* cost) {
-  int best = -1;
-  for (int i = 0; i < num_tiles(bits); ++i) {
-    const Tile t = tile_at(bits, i);
-    if (in_range && tiles_per_cu(t, M, N) > 3 * (t.resident > 2 ? t.resident : 2)) continue;
-    const double c = tile_cost(t, M, N, K);
-    if (best < 0 || c < *cost) {
-      best = i;
-      *cost = c;
-    }
-  }
-  return best;
-}
-
 template <int BITS, bool ACC_OUT, bool WA8, bool ZP>
-void launch_canonical(const KsplitCall& c, hipStream_t stream) {
-  if (c.M <= 16) {
-    launch_decode<BITS, ACC_OUT, WA8, ZP, false>(c, stream);
-    return;
-  }
-  double cost;
-  int tile = best_tile(c.M, c.N, c.K, BITS, true, &cost);
-  if (tile < 0) tile = best_tile(c.M, c.N, c.K, BITS, false, &cost);
-  launch_tile<BITS, ACC_OUT, WA8, ZP>(tile, c, stream);
+void launch_canonical(const KsplitCall& c, int tile, hipStream_t stream) {
+  if (c.M <= 16) launch_decode<BITS, ACC_OUT, WA8, ZP, false>(c, stream);
+  else launch_tile<BITS, ACC_OUT, WA8, ZP>(tile, c, stream);
 }
 
 }  // namespace
 
-double ksplit_cost(int64_t M, int64_t N, int K, int bits) {
-  double cost;
-  return best_tile(M, N, K, bits, true, &cost) < 0 ? HUGE_VAL : cost;
-}
-
-hipError_t launch_ksplit(const KsplitCall& c, int bits, int weights, hipStream_t stream) {
+hipError_t launch_ksplit(const KsplitCall& c, int bits, int weights, int tile, hipStream_t stream) {
   if (c.M == 0) return hipSuccess;
+  if (c.M > 16 && tile < 0) return hipErrorInvalidValue;
   const bool acc = c.acc != nullptr, zp = c.a_zeros != nullptr;
   if (weights == kWeightsDecode) {
     if (bits == 4) acc ? launch_decode<4, true, false, false, true>(c, stream)
@@ -513,15 +423,15 @@ hipError_t launch_ksplit(const KsplitCall& c, int bits, int weights, hipStream_t
     else acc ? launch_decode<8, true, false, false, true>(c, stream)
              : launch_decode<8, false, false, false, true>(c, stream);
   } else if (weights == kWeightsA8Order) {
-    launch_canonical<8, false, true, false>(c, stream);
+    launch_canonical<8, false, true, false>(c, tile, stream);
   } else if (bits == 4) {
-    if (acc) launch_canonical<4, true, false, false>(c, stream);
-    else if (zp) launch_canonical<4, false, false, true>(c, stream);
-    else launch_canonical<4, false, false, false>(c, stream);
+    if (acc) launch_canonical<4, true, false, false>(c, tile, stream);
+    else if (zp) launch_canonical<4, false, false, true>(c, tile, stream);
+    else launch_canonical<4, false, false, false>(c, tile, stream);
   } else {
-    if (acc) launch_canonical<8, true, false, false>(c, stream);
-    else if (zp) launch_canonical<8, false, false, true>(c, stream);
-    else launch_canonical<8, false, false, false>(c, stream);
+    if (acc) launch_canonical<8, true, false, false>(c, tile, stream);
+    else if (zp) launch_canonical<8, false, false, true>(c, tile, stream);
+    else launch_canonical<8, false, false, false>(c, tile, stream);
   }
   return hipGetLastError();
 }

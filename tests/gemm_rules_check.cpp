@@ -1,0 +1,58 @@
+// Prints the routes of the GEMM dispatch rules for shapes read from stdin, at 256
+// compute units:
+//   int8 M N K bits -> the kernel (decode, tile, wide or ksplit), and for ksplit
+//                      its tile as TI x TJ x wavefronts;
+//   fp6 M N K       -> wide, or TI x TJ x wavefronts x stages;
+//   decode N        -> the K-split kernel's workgroup for M <= 16;
+//   tiles           -> every tile of the tables, one a line, then an empty line.
+#include "gemm_rules.h"
+
+#include <cstdio>
+#include <cstring>
+
+using namespace dptq;
+using namespace dptq::rules;
+
+int main() {
+  const int cus = 256;
+  char what[16];
+  while (std::scanf("%15s", what) == 1) {
+    long M = 0, N = 0;
+    int K = 0, bits = 0;
+    if (!std::strcmp(what, "int8")) {
+      if (std::scanf("%ld %ld %d %d", &M, &N, &K, &bits) != 4) return 1;
+      const GemmRoute r = gemm_route(M, N, K, bits, cus);
+      if (r.kernel == kGemmKsplit) {
+        const KsplitTile t = ksplit_tile(bits, r.tile);
+        std::printf("ksplit %dx%dx%d\n", t.ti, t.tj, t.waves);
+      } else {
+        std::printf("%s\n", r.kernel == kGemmDecode ? "decode" : r.kernel == kGemmWide ? "wide" : "tile");
+      }
+    } else if (!std::strcmp(what, "fp6")) {
+      if (std::scanf("%ld %ld %d", &M, &N, &K) != 3) return 1;
+      const int i = fp6_ksplit_or_none(M, N, K, cus);
+      if (i < 0) {
+        std::printf("wide\n");
+      } else {
+        const Fp6KsplitTile t = kFp6KsplitTiles[i];
+        std::printf("ksplit %dx%dx%dx%d\n", t.ti, t.tj, t.waves, t.bufs);
+      }
+    } else if (!std::strcmp(what, "decode")) {
+      if (std::scanf("%ld", &N) != 1) return 1;
+      const DecodeTile t = decode_tile(N, cus);
+      std::printf("%dx1x%d\n", t.ti, t.waves);
+    } else if (!std::strcmp(what, "tiles")) {
+      for (int b = 4; b <= 8; b += 4)
+        for (int i = 0; i < ksplit_tiles(b); ++i) {
+          const KsplitTile t = ksplit_tile(b, i);
+          std::printf("int8 %d %dx%dx%d\n", b, t.ti, t.tj, t.waves);
+        }
+      for (const Fp6KsplitTile& t : kFp6KsplitTiles)
+        std::printf("fp6 4 %dx%dx%dx%d\n", t.ti, t.tj, t.waves, t.bufs);
+      std::printf("\n");
+    } else {
+      return 1;
+    }
+  }
+  return 0;
+}

@@ -1,0 +1,38 @@
+"""The GEMM dispatch rules (csrc/gemm_rules.h) in a host build: no GPU needed."""
+
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    """The routes of a list of queries (tests/gemm_rules_check.cpp), a list of lines."""
+    gxx = shutil.which("g++")
+    if not gxx:
+        pytest.skip("g++ not available")
+    exe = tmp_path_factory.mktemp("rules") / "gemm_rules_check"
+    r = subprocess.run([gxx, "-O1", "-std=c++17", "-Wall", "-Werror",
+                        "-I" + os.path.join(ROOT, "paper_2606_12487_amd", "csrc"),
+                        os.path.join(ROOT, "tests", "gemm_rules_check.cpp"), "-o", str(exe)],
+                       capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr[-2000:]
+
+    def ask(queries):
+        run = subprocess.run([str(exe)], input="\n".join(queries) + "\n", capture_output=True, text=True,
+                             timeout=60)
+        assert run.returncode == 0, run.stdout[-2000:]
+        return run.stdout.rstrip("\n").split("\n")
+
+    return ask
+
+
+def test_every_shape_has_a_kernel(routes):
+    # Sizes far beyond the fitted ones keep to the tile kernels.
+    assert routes(["int8 16 4096 4096 4", "int8 17 16 128 8", "int8 1000000 57344 65536 4",
+                   "int8 100000 176 8192 8", "fp6 1000000 57344 65536"]) == [
+                       "decode", "ksplit 1x2x8", "wide", "tile", "wide"]
