@@ -183,31 +183,32 @@ constexpr Fp6KsplitTile kFp6KsplitTiles[] = {
     {4, 4, 4, 1, 1, 1.83, 4.98, 1.99e-3, 0.0, 4.41e-8, 7.70e-7}};
 constexpr int kNumFp6KsplitTiles = sizeof(kFp6KsplitTiles) / sizeof(kFp6KsplitTiles[0]);
 
-// The tile with the lowest estimate; those that run more than three rounds lie
-// beyond the fitted shapes and count only with any_size.
-inline TilePlan fp6_ksplit_plan(int64_t M, int64_t N, int K, bool any_size, int cus) {
+// The tile with the lowest estimate among those that run at most three rounds,
+// where the fitted shapes lie.
+inline TilePlan fp6_ksplit_plan(int64_t M, int64_t N, int K, int cus) {
   TilePlan best{-1, 0.0};
   for (int i = 0; i < kNumFp6KsplitTiles; ++i) {
     const Fp6KsplitTile& t = kFp6KsplitTiles[i];
     const int64_t q = ceil_div(ceil_div(ceil_div(M, 32), t.tj) * ceil_div(ceil_div(N, 32), t.ti), cus);
-    if (!any_size && q > 3 * t.resident) continue;
+    if (q > 3 * t.resident) continue;
     const double c = ksplit_tile_us(t, q, M, N, K);
     if (best.tile < 0 || c < best.cost) best = {i, c};
   }
   return best;
 }
 
-// The K-split kernel's tile, or -1 for the 192 x 256 kernel.  That kernel takes
-// at least one full tile of padded rows each way and three stages per tile; of
-// those shapes it runs the ones whose estimate (whole rounds of its tiles, 6.9
-// us + 4.0 ns per k each, and the operands' and the output's way) the K-split
-// kernel's is not at least 5% below.
+// The K-split kernel's tile where its estimate is at least 5% below the 192 x 256
+// kernel's (whole rounds of its tiles, 6.9 us + 4.0 ns per k each, and the
+// operands' and the output's way), or -1 for that kernel.  The line is the same
+// for the shapes below one of its tiles or three of its stages, which run its
+// clamped variant: M = 4096, N = 28672, K = 256 72 us there against 131 us on the
+// K-split kernel, M = 224, N = 28672, K = 4096 35.6 against 43.5 us, but M = 64,
+// N = 2048, K = 14336 80.4 against 9.9 us.
 inline int fp6_ksplit_or_none(int64_t M, int64_t N, int K, int cus) {
-  const bool fits = ceil_div(M, 32) >= 8 && ceil_div(N, 32) >= 6 && K >= 3 * 128;
   const double rounds = (double)ceil_div(ceil_div(M, 256) * ceil_div(N, 192), cus), k = (double)K, n = (double)N;
   const double cost = rounds * (6.91 + 3.99e-3 * k) + 5.98e-8 * k * n + 1.84e-7 * (double)M * n;
-  const TilePlan p = fp6_ksplit_plan(M, N, K, !fits, cus);
-  return p.tile >= 0 && (!fits || p.cost < 0.95 * cost) ? p.tile : -1;
+  const TilePlan p = fp6_ksplit_plan(M, N, K, cus);
+  return p.tile >= 0 && p.cost < 0.95 * cost ? p.tile : -1;
 }
 
 }  // namespace rules

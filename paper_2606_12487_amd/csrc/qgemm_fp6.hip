@@ -178,10 +178,11 @@ constexpr int f6_part_after(int f, int frags, int parts) {
   return 0;
 }
 
-// Body of the GEMM for wavefront WV of a workgroup.  Shapes have at least one
-// full tile of padded rows each way and three stages per tile; edge tiles are
-// shifted inward so every load is a base plus a constant.
-template <int WV, bool ACC_OUT>
+// Body of the GEMM for wavefront WV of a workgroup.  Fast shapes (at least
+// one full tile of padded rows each way and three stages per tile) shift edge
+// tiles inward so every load is a base plus a constant; the CLAMP variant
+// (small shapes) clamps each block row instead.
+template <int WV, bool ACC_OUT, bool CLAMP>
 __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
                                                const float* __restrict__ a_scales,
                                                const uint8_t* __restrict__ w6,
@@ -217,8 +218,10 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
     const int tn = t / gm, tm = g * kGroupM + (t - tn * gm);
     m0 = tm * C::kBM;
     n0 = tn * C::kBN;
-    m0 = min(m0, mblk * 32 - C::kBM);
-    n0 = min(n0, nblk * 32 - C::kBN);
+    if constexpr (!CLAMP) {
+      m0 = min(m0, mblk * 32 - C::kBM);
+      n0 = min(n0, nblk * 32 - C::kBN);
+    }
   };
 
   const uint32_t smem_base = (uint32_t)(uintptr_t)(lds_ptr_t)smem;
@@ -229,26 +232,42 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
   // into ring buffer buf.  Load q < 18 is part q % 3 of weight block q / 3,
   // load q >= 18 part of activation block (q - 18) / 3; it lands at q KiB.
   // Loads P0 .. P1 - 1 of this wavefront's NL.
-  auto issue_part = [&](const uint8_t* wt, const uint8_t* at, int kb, int buf, auto p0c, auto p1c) __attribute__((always_inline)) {
+  auto issue_part = [&](const uint8_t* wt, const uint8_t* at, int rbw, int rba, int kb, int buf, auto p0c,
+                        auto p1c) __attribute__((always_inline)) {
     constexpr int P0 = decltype(p0c)::value, P1 = decltype(p1c)::value;
     const uint8_t* wst = wt + (size_t)kb * wstride;
     const uint8_t* ast = at + (size_t)kb * astride;
     const uint32_t base = smem_base + buf * C::kStage;
-    // Contiguous: load q reads 1 KiB at a constant offset from the stage base.
-    auto one = [&](auto qc) __attribute__((always_inline)) {
-      constexpr int q = decltype(qc)::value;
-      constexpr int rel = q < C::kWLoads ? q : q - C::kWLoads;
-      // The block offset travels in the per-lane offset (one vector
-      // instruction) and the LDS offset in M0's add, so a load costs one
-      // scalar instruction beside it.
-      f6_dma16_at<(uint32_t)(q * 1024)>(q < C::kWLoads ? wst : ast, lane16 + (uint32_t)(rel * 1024), base);
-    };
-    [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
-      (one(std::integral_constant<int, Q0 + P0 + I>{}), ...);
-    }(std::make_integer_sequence<int, P1 - P0>{});
+    if constexpr (!CLAMP) {
+      // Contiguous: load q reads 1 KiB at a constant offset from the stage base.
+      auto one = [&](auto qc) __attribute__((always_inline)) {
+        constexpr int q = decltype(qc)::value;
+        constexpr int rel = q < C::kWLoads ? q : q - C::kWLoads;
+        // The block offset travels in the per-lane offset (one vector
+        // instruction) and the LDS offset in M0's add, so a load costs one
+        // scalar instruction beside it.
+        f6_dma16_at<(uint32_t)(q * 1024)>(q < C::kWLoads ? wst : ast, lane16 + (uint32_t)(rel * 1024), base);
+      };
+      [&]<int... I>(std::integer_sequence<int, I...>) __attribute__((always_inline)) {
+        (one(std::integral_constant<int, Q0 + P0 + I>{}), ...);
+      }(std::make_integer_sequence<int, P1 - P0>{});
+    } else {
+#pragma unroll
+      for (int i = P0; i < P1; ++i) {
+        const int q = Q0 + i;
+        const bool isa = q >= C::kWLoads;
+        const int qq = isa ? q - C::kWLoads : q;
+        const int b = qq / 3;
+        const int rb = isa ? min(rba + b, mblk - 1) : min(rbw + b, nblk - 1);
+        const uint8_t* src = (isa ? a6 + (size_t)kb * astride : w6 + (size_t)kb * wstride) +
+                             (uint32_t)(rb * kF6Block + (qq - 3 * b) * 1024);
+        f6_dma16(src, lane16, base + q * 1024);
+      }
+    }
   };
-  auto issue = [&](const uint8_t* wt, const uint8_t* at, int kb, int buf) __attribute__((always_inline)) {
-    issue_part(wt, at, kb, buf, std::integral_constant<int, 0>{}, std::integral_constant<int, NL>{});
+  auto issue = [&](const uint8_t* wt, const uint8_t* at, int rbw, int rba, int kb, int buf)
+      __attribute__((always_inline)) {
+    issue_part(wt, at, rbw, rba, kb, buf, std::integral_constant<int, 0>{}, std::integral_constant<int, NL>{});
   };
   // Scales of tile r into slot r & 1 (only when producing y): wavefront 0
   // loads a_s [256], wavefront 1 w_s [192], 4 bytes per lane, rows clamped.
@@ -305,7 +324,8 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
   // this stage's buffer and the next stage is read into nxt, all between
   // this stage's 24 MFMAs.  The scheduling fences keep that order.
   constexpr int kParts = 5;   // parts a stage's loads are issued in
-  auto stage = [&](const Frag& cur, Frag& nxt, int buf, const uint8_t* wt, const uint8_t* at, int kbi) __attribute__((always_inline)) {
+  auto stage = [&](const Frag& cur, Frag& nxt, int buf, const uint8_t* wt, const uint8_t* at,
+                   int rbw, int rba, int kbi) __attribute__((always_inline)) {
     const int nbuf = buf == 2 ? 0 : buf + 1;
     f6_wait_lgkm0();
     f6_wait_vmcnt<NL>();
@@ -317,7 +337,7 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
     // [k NL / kParts, (k + 1) NL / kParts) and follows read k * kFrags / kParts - 1.
     constexpr int kFrags = 2 * (kTI + kTJ);
     const uint8_t* s = smem + nbuf * C::kStage;
-    issue_part(wt, at, kbi, buf, std::integral_constant<int, 0>{},
+    issue_part(wt, at, rbw, rba, kbi, buf, std::integral_constant<int, 0>{},
                std::integral_constant<int, NL / kParts>{});
     [&]<int... F>(std::integer_sequence<int, F...>) __attribute__((always_inline)) {
       (
@@ -329,7 +349,7 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
               read_frag(s + st * 1536 + kAOff + (x - kTI) * kF6Block, nxt.a[st][x - kTI]);
             constexpr int k = f6_part_after(F, kFrags, kParts);
             if constexpr (k > 0)
-              issue_part(wt, at, kbi, buf, std::integral_constant<int, k * NL / kParts>{},
+              issue_part(wt, at, rbw, rba, kbi, buf, std::integral_constant<int, k * NL / kParts>{},
                          std::integral_constant<int, (k + 1) * NL / kParts>{});
           }(),
           ...);
@@ -399,27 +419,38 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
     }
   };
 
-  // Issue targets.  A stage issued three ahead is in the current tile or the
-  // next (a tile has at least three stages); past the workgroup's last stage
-  // the last stage is issued again into a buffer nobody reads any more, so
-  // every stage issues the same loads.
+  // Issue targets.  In the fast shapes a stage issued three ahead is in the
+  // current tile or the next (a tile has at least three stages); past the
+  // workgroup's last stage the last stage is issued again into a buffer
+  // nobody reads any more, so every stage issues the same loads.  The CLAMP
+  // variant looks up any tile up to three ahead.
   struct Tgt {
     const uint8_t* wt;
     const uint8_t* at;
-    int kb;
+    int rbw, rba, kb;
   };
   auto tile_base = [&](int r, Tgt& tg) __attribute__((always_inline)) {
     int m0, n0;
     origin(r, m0, n0);
-    tg.wt = w6 + (size_t)(n0 / 32) * kF6Block;
-    tg.at = a6 + (size_t)(m0 / 32) * kF6Block;
+    tg.rbw = n0 / 32;
+    tg.rba = m0 / 32;
+    tg.wt = w6 + (size_t)tg.rbw * kF6Block;
+    tg.at = a6 + (size_t)tg.rba * kF6Block;
   };
   auto target = [&](int r, int kb, const Tgt& cur_t, const Tgt& next_t) __attribute__((always_inline)) {
+    Tgt tg;
     const int k3 = kb + 3;
-    const bool in_next = k3 >= nkb;
-    const bool has_next = r + 1 < ntile;
-    Tgt tg = (in_next && has_next) ? next_t : cur_t;
-    tg.kb = in_next ? (has_next ? k3 - nkb : nkb - 1) : k3;
+    if constexpr (!CLAMP) {
+      const bool in_next = k3 >= nkb;
+      const bool has_next = r + 1 < ntile;
+      tg = (in_next && has_next) ? next_t : cur_t;
+      tg.kb = in_next ? (has_next ? k3 - nkb : nkb - 1) : k3;
+    } else {
+      const int w = (k3 >= nkb) + (k3 >= 2 * nkb) + (k3 >= 3 * nkb);
+      const bool past = r + w >= ntile;
+      tile_base(past ? ntile - 1 : r + w, tg);
+      tg.kb = past ? nkb - 1 : k3 - w * nkb;
+    }
     return tg;
   };
 
@@ -431,7 +462,7 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const Tgt tg = target(0, i - 3, t_cur, t_next);
-    issue(tg.wt, tg.at, tg.kb, i);
+    issue(tg.wt, tg.at, tg.rbw, tg.rba, tg.kb, i);
   }
   // Stage 0 has landed once only stages 1 and 2 are outstanding.
   f6_wait_vmcnt<2 * NL>();
@@ -456,15 +487,15 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
     int kb = 0;
     for (; kb + 1 < nkb; kb += 2) {
       Tgt tg = target(r, kb, t_cur, t_next);
-      stage(fa, fb, buf, tg.wt, tg.at, tg.kb);
+      stage(fa, fb, buf, tg.wt, tg.at, tg.rbw, tg.rba, tg.kb);
       buf = buf == 2 ? 0 : buf + 1;
       tg = target(r, kb + 1, t_cur, t_next);
-      stage(fb, fa, buf, tg.wt, tg.at, tg.kb);
+      stage(fb, fa, buf, tg.wt, tg.at, tg.rbw, tg.rba, tg.kb);
       buf = buf == 2 ? 0 : buf + 1;
     }
     if (kb < nkb) {
       const Tgt tg = target(r, kb, t_cur, t_next);
-      stage(fa, fb, buf, tg.wt, tg.at, tg.kb);
+      stage(fa, fb, buf, tg.wt, tg.at, tg.rbw, tg.rba, tg.kb);
       buf = buf == 2 ? 0 : buf + 1;
       fa = fb;
     }
@@ -480,17 +511,17 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
   f6_wait_vmcnt<0>();   // the re-issued tail loads land before the LDS is released
 }
 
-template <bool ACC_OUT>
+template <bool ACC_OUT, bool CLAMP>
 __global__ void __launch_bounds__(256)
 qgemm_fp6(const uint8_t* __restrict__ a6, const float* __restrict__ a_scales,
           const uint8_t* __restrict__ w6, const float* __restrict__ w_scales, int M, int N,
           int K, __half* __restrict__ y, int32_t* __restrict__ acc_out) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[F6::kLds];
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: qgemm_fp6_body<0, ACC_OUT>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
-    case 1: qgemm_fp6_body<1, ACC_OUT>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
-    case 2: qgemm_fp6_body<2, ACC_OUT>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
-    default: qgemm_fp6_body<3, ACC_OUT>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
+    case 0: qgemm_fp6_body<0, ACC_OUT, CLAMP>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
+    case 1: qgemm_fp6_body<1, ACC_OUT, CLAMP>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
+    case 2: qgemm_fp6_body<2, ACC_OUT, CLAMP>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
+    default: qgemm_fp6_body<3, ACC_OUT, CLAMP>(a6, a_scales, w6, w_scales, M, N, K, y, acc_out, smem); break;
   }
 }
 
@@ -515,13 +546,25 @@ hipError_t launch_qlinear_fp6(const uint8_t* a6, const float* a_scales, int64_t 
   if (tile >= 0) return launch_fp6_ksplit(tile, a6, a_scales, M, K, w6, w_scales, N, y, out_acc, stream);
   const int64_t tiles = ((M + F6::kBM - 1) / F6::kBM) * ((N + F6::kBN - 1) / F6::kBN);
   const int64_t grid = tiles < cus ? tiles : cus;
+  // Fast shapes: at least one full tile of padded rows each way and three
+  // stages per tile.
+  const bool clamp = (M + 31) / 32 < F6::kABlk || (N + 31) / 32 < F6::kWBlk || K < 3 * 128;
   __half* yh = static_cast<__half*>(y);
-  if (out_acc)
-    hipLaunchKernelGGL((qgemm_fp6<true>), dim3((unsigned)grid), dim3(256), 0, stream, a6, a_scales, w6,
-                       w_scales, (int)M, (int)N, K, yh, out_acc);
-  else
-    hipLaunchKernelGGL((qgemm_fp6<false>), dim3((unsigned)grid), dim3(256), 0, stream, a6, a_scales, w6,
-                       w_scales, (int)M, (int)N, K, yh, out_acc);
+  if (out_acc) {
+    if (clamp)
+      hipLaunchKernelGGL((qgemm_fp6<true, true>), dim3((unsigned)grid), dim3(256), 0, stream, a6,
+                         a_scales, w6, w_scales, (int)M, (int)N, K, yh, out_acc);
+    else
+      hipLaunchKernelGGL((qgemm_fp6<true, false>), dim3((unsigned)grid), dim3(256), 0, stream, a6,
+                         a_scales, w6, w_scales, (int)M, (int)N, K, yh, out_acc);
+  } else {
+    if (clamp)
+      hipLaunchKernelGGL((qgemm_fp6<false, true>), dim3((unsigned)grid), dim3(256), 0, stream, a6,
+                         a_scales, w6, w_scales, (int)M, (int)N, K, yh, out_acc);
+    else
+      hipLaunchKernelGGL((qgemm_fp6<false, false>), dim3((unsigned)grid), dim3(256), 0, stream, a6,
+                         a_scales, w6, w_scales, (int)M, (int)N, K, yh, out_acc);
+  }
   return hipGetLastError();
 }
 

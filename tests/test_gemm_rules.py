@@ -36,3 +36,14 @@ def test_every_shape_has_a_kernel(routes):
     assert routes(["int8 16 4096 4096 4", "int8 17 16 128 8", "int8 1000000 57344 65536 4",
                    "int8 100000 176 8192 8", "fp6 1000000 57344 65536"]) == [
                        "decode", "ksplit 1x2x8", "wide", "tile", "wide"]
+
+
+def test_fp6_shapes_of_the_tile_kernel(routes):
+    # Short K, few channels for many rows, and almost a tile of rows: measured 1.1
+    # to 2.3 times slower on the K-split kernel.
+    slow = ["fp6 4096 28672 256", "fp6 65536 2576 128", "fp6 65536 160 4096", "fp6 224 28672 4096",
+            "fp6 224 57344 512", "fp6 160 28672 2048", "fp6 1024 57344 128"]
+    fast = ["fp6 500 4096 4096", "fp6 64 2048 14336", "fp6 33 28672 256", "fp6 100 160 4096"]
+    got = routes(slow + fast)
+    assert got[:len(slow)] == ["wide"] * len(slow)
+    assert all(r.startswith("ksplit") for r in got[len(slow):]), got

@@ -30,6 +30,8 @@ CASES = [
     (258, 10016, 1408),    # 4 x 3, 4
     (331, 8416, 2048),     # 4 x 4, 4: the sum takes several passes
     (517, 10928, 384),     # the 192 x 256 kernel at its fewest stages
+    # its clamped variant: one and two stages, too few rows, too few channels
+    (777, 11024, 128), (1029, 6160, 256), (217, 28688, 384), (65569, 160, 128),
 ]
 
 
