@@ -197,18 +197,30 @@ inline TilePlan fp6_ksplit_plan(int64_t M, int64_t N, int K, int cus) {
   return best;
 }
 
-// The K-split kernel's tile where its estimate is at least 5% below the 192 x 256
-// kernel's (whole rounds of its tiles, 6.9 us + 4.0 ns per k each, and the
-// operands' and the output's way), or -1 for that kernel.  The line is the same
-// for the shapes below one of its tiles or three of its stages, which run its
+// The K-split kernel's tile where its estimate is below the 192 x 256 kernel's
+// (whole rounds of its tiles, 6.9 us + 4.0 ns per k each, and the operands' and
+// the output's way) by a margin, or -1 for that kernel.  The margin is 5%, and
+// 10% for the shapes below one of its tiles or three of its stages, which run its
 // clamped variant: M = 4096, N = 28672, K = 256 72 us there against 131 us on the
 // K-split kernel, M = 224, N = 28672, K = 4096 35.6 against 43.5 us, but M = 64,
 // N = 2048, K = 14336 80.4 against 9.9 us.
+//
+// Beyond the fitted M the activations count: the K-split kernel's tiles run
+// along M within an XCD, so up to eight L2s read all of them, and each read past
+// the second adds 6e-8 us an element (M = 8192, N = 512, K = 2048 20.4 against
+// 16.2 us on the 192 x 256 kernel, M = 4096, N = 1024, K = 2048 20.0 against 16.2,
+// K = 14336 58 against 80).
 inline int fp6_ksplit_or_none(int64_t M, int64_t N, int K, int cus) {
+  const bool fits = ceil_div(M, 32) >= 8 && ceil_div(N, 32) >= 6 && K >= 3 * 128;
   const double rounds = (double)ceil_div(ceil_div(M, 256) * ceil_div(N, 192), cus), k = (double)K, n = (double)N;
   const double cost = rounds * (6.91 + 3.99e-3 * k) + 5.98e-8 * k * n + 1.84e-7 * (double)M * n;
-  const TilePlan p = fp6_ksplit_plan(M, N, K, cus);
-  return p.tile >= 0 && p.cost < 0.95 * cost ? p.tile : -1;
+  TilePlan p = fp6_ksplit_plan(M, N, K, cus);
+  if (p.tile < 0) return -1;
+  if (M > 2048) {
+    const int64_t tn = ceil_div(ceil_div(N, 32), kFp6KsplitTiles[p.tile].ti), reads = tn < 8 ? tn : 8;
+    if (reads > 2) p.cost += 6e-8 * k * (double)M * (double)(reads - 2);
+  }
+  return p.cost < (fits ? 0.95 : 0.9) * cost ? p.tile : -1;
 }
 
 }  // namespace rules

@@ -43,7 +43,11 @@ def test_fp6_shapes_of_the_tile_kernel(routes):
     # to 2.3 times slower on the K-split kernel.
     slow = ["fp6 4096 28672 256", "fp6 65536 2576 128", "fp6 65536 160 4096", "fp6 224 28672 4096",
             "fp6 224 57344 512", "fp6 160 28672 2048", "fp6 1024 57344 128"]
-    fast = ["fp6 500 4096 4096", "fp6 64 2048 14336", "fp6 33 28672 256", "fp6 100 160 4096"]
+    # Many rows of few channels: up to 1.26 times slower there.
+    slow += ["fp6 8192 512 2048", "fp6 4096 1024 2048", "fp6 16384 256 1536", "fp6 6144 768 1024",
+             "fp6 6144 2048 8192", "fp6 160 28672 8192"]
+    fast = ["fp6 500 4096 4096", "fp6 64 2048 14336", "fp6 33 28672 256", "fp6 100 160 4096",
+            "fp6 4096 512 2048", "fp6 16384 160 512"]
     got = routes(slow + fast)
     assert got[:len(slow)] == ["wide"] * len(slow)
     assert all(r.startswith("ksplit") for r in got[len(slow):]), got
