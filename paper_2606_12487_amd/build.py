@@ -24,8 +24,8 @@ LIB_PATH = os.path.join(PKG_DIR, "libdptq.so")
 BINDING_SOURCE = os.path.join(CSRC, "torch_binding.cpp")
 BINDING_PATH = os.path.join(PKG_DIR, "_dptq_torch.so")
 
-SOURCES = ["rotate_quant.hip", "decode_fused.hip", "qgemm_ksplit.hip", "range_quant.hip", "qgemm.hip", "qgemm_fp6.hip", "qgemm_fp6_ksplit.hip",
-           "kv_quant.hip", "dptq_api.hip"]
+SOURCES = ["rotate_quant.hip", "decode_fused.hip", "qgemm_ksplit.hip", "range_quant.hip",
+           "qgemm.hip", "qgemm_decode.hip", "qgemm_fp6.hip", "qgemm_fp6_ksplit.hip", "kv_quant.hip", "dptq_api.hip"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [

@@ -142,6 +142,10 @@ inline GemmRoute gemm_route(int64_t M, int64_t N, int K, int bits, int cus) {
   return {wide ? kGemmWide : kGemmTile, -1};
 }
 
+// ---------------------------------------------------------------------------
+// At most 16 tokens: the K-split kernel, or the kernel that streams the weights
+// into registers (qgemm_decode.hip).
+// ---------------------------------------------------------------------------
 // Workgroup of the K-split kernel for at most 16 tokens, as blocks of 16 channels
 // and wavefronts: one block while these fit the compute units (about) once, two
 // on eight wavefronts while those do, then two on four wavefronts (several
@@ -159,6 +163,94 @@ inline DecodeTile decode_tile(int64_t N, int cus) {
   if (8 * nb <= 9 * (int64_t)cus) return {1, 8};
   if (nb > 2 * (int64_t)cus && nb <= 4 * (int64_t)cus) return {2, 4};
   return {2, 8};
+}
+
+// Blocks of 16 output channels per workgroup of the register kernel.  A
+// one-block workgroup reads M * K * bits / 8 activation bytes beside 8 K weight
+// bytes; once the activations are as large (M * bits >= 64) two blocks share
+// them, provided N still gives two workgroups per compute unit.  (Four blocks
+// were slower at 8 tokens and 4 bits, N = 57344.)
+inline int decode_blocks(int64_t M, int64_t N, int bits, int cus) {
+  return M * bits >= 64 && N % 32 == 0 && N / 32 >= 2 * (int64_t)cus ? 2 : 1;
+}
+// Its 128-k chunks in flight: eight instead of four where a wavefront streams
+// at least 12, the grid is at most one workgroup per compute unit and M <= 4
+// (decode layout, K = 14336, N = 4096, 4 bits: M = 1 7.90 -> 7.25 us, M = 4 8.30
+// -> 7.40 us); slower with fewer chunks or more workgroups (K = 4096, N = 12288,
+// M = 1: 6.53 -> 8.25 us).
+inline int decode_batch(int64_t M, int64_t N, int K, int blocks, int cus) {
+  return blocks == 1 && M <= 4 && K / 128 >= 12 * 8 && N / 16 <= cus ? 8 : 4;
+}
+
+// Estimated microseconds of either on the decode layout: a start, then what grows
+// with the workgroups of the fullest compute unit, with their batches of four
+// chunks (stages of the K-split kernel), with the rounds of `resident` workgroups
+// a compute unit, with a wavefront's chunks (stages), and the weights' and the
+// activations' way.  Fitted where they decide (below), to 2128 and 2128 shapes a
+// bit width (M 1-16, N 64-57344, K 512-28672; weights cycling through 768 MB),
+// within 3 to 7% (one standard deviation).
+struct DecodeCost {
+  int resident;
+  double start, wg, wg_step, round, round_step, step, kn, act;
+};
+constexpr DecodeCost kDecodeCosts[2][6] = {
+    // 4 bits: registers 1 x 4, 1 x 8 and 2 x 4 (blocks x chunks), K split 1 x 8, 2 x 4 and 2 x 8
+    {{1, 2.385, 0, 0.2755, 0, 0, 0.0722, 5.77e-8, 7.12e-6},
+     {1, 0, 0, 0, 2.04, 0.566, 0.0363, 4.31e-8, 5.68e-6},
+     {3, 2.385, 0, 0.2283, 0.2143, 0, 0.0582, 4.46e-8, 2.011e-5},
+     {1, 2.467, 0, 0, 0, 0, 0.2914, 6.64e-8, 1.05e-6},
+     {1, 0, 1.44, 0.1117, 0, 0, 0, 6.98e-8, 2.55e-6},
+     {3, 2.374, 0.0681, 0.1693, 0.2595, 0, 0.0795, 7.07e-8, 3.04e-6}},
+    // 8 bits
+    {{1, 2.252, 0, 0.3416, 0.0292, 0, 0.1009, 5.19e-8, 1.47e-5},
+     {1, 0, 0, 0, 2.049, 0, 0.2089, 5.38e-8, 1.559e-5},
+     {2, 1.754, 0, 0, 1.082, 0.2134, 0.1214, 5.96e-8, 1.678e-5},
+     {1, 2.498, 0, 0.3315, 0, 0, 0, 6.43e-8, 2.98e-6},
+     {1, 0, 1.454, 0.1662, 0, 0, 0, 6.10e-8, 6.96e-6},
+     {2, 1.891, 0.1828, 0.2512, 0.5839, 0, 0.1412, 6.11e-8, 6.75e-6}}};
+inline double decode_us(const DecodeCost& c, int64_t wgs, int64_t steps, int64_t wg_steps, int64_t M, int64_t N,
+                        int K, int cus) {
+  const double q = (double)ceil_div(wgs, cus), rounds = (double)ceil_div(wgs, (int64_t)cus * c.resident);
+  const double k = (double)K, ws = (double)wg_steps;
+  return c.start + q * (c.wg + c.wg_step * ws) + rounds * (c.round + c.round_step * ws) + c.step * (double)steps +
+         c.kn * k * (double)N + c.act * q * (double)M * k;
+}
+inline double decode_regs_us(int64_t M, int64_t N, int K, int bits, int cus) {
+  const int blocks = decode_blocks(M, N, bits, cus), batch = decode_batch(M, N, K, blocks, cus);
+  const int64_t chunks = ceil_div(K / 128, 8);
+  return decode_us(kDecodeCosts[bits == 8][blocks == 2 ? 2 : batch == 8 ? 1 : 0], N / (16 * blocks), chunks,
+                   ceil_div(chunks, batch) * (batch / 4), M, N, K, cus);
+}
+inline double decode_ksplit_us(int64_t M, int64_t N, int K, int bits, int cus) {
+  const DecodeTile t = decode_tile(N, cus);
+  const int64_t stages = ceil_div(ceil_div(K, 256), t.waves);
+  return decode_us(kDecodeCosts[bits == 8][t.ti == 1 ? 3 : t.waves == 4 ? 4 : 5], ceil_div(N / 16, t.ti), stages,
+                   stages, M, N, K, cus);
+}
+
+// Which of the two.  Where a wavefront has at most half a chunk the way through
+// LDS only adds latency: K <= 128, or K <= 512 on at most two blocks of channels
+// a compute unit (M = 1, N = 4096, K = 512, 8 bits: 2.75 against 2.99 us); but
+// three of the register kernel's workgroups fit a compute unit at 8 bits, so
+// between three and four blocks it loses a round (M = 4, N = 14336, K = 128: 3.4
+// against 3.1 us).  Longer rows of canonical weights take the K-split kernel,
+// whose loads cover whole lines (M = 4, N = 4096, K = 14336, 8 bits: 8.7 against
+// 10.6 us).  The decode layout gives both kernels whole KiB, so the estimates
+// decide (4 bits: M = 1, N = 2560, K = 14336 6.5 us in registers against 7.6 us, M =
+// 1, N = 28672, K = 4096 11.6 against 13.7, M = 16, N = K = 8192 10.1 against 8.9),
+// but for short rows of many channels, which the K-split kernel takes (M = 1, N =
+// 43008, K = 768: 8.1 against 9.5 us), and long rows that the register kernel
+// streams eight chunks at a time at 4 bits (M = 1, N = 1024, K = 28672: 9.4
+// against 11.4 us, N = 4096, K = 14336 7.5 against 8.0).
+inline bool decode_in_regs(int64_t M, int64_t N, int K, int bits, bool decode_layout, int cus) {
+  const int64_t nb = N / 16;
+  const bool many = nb > 2 * (int64_t)cus;
+  if (K <= 128) return !(bits == 8 && nb > 3 * (int64_t)cus && nb <= 4 * (int64_t)cus);
+  if (K <= 512 && !many) return true;
+  if (!decode_layout) return bits == 8 && K <= 384 && nb > 4 * (int64_t)cus;
+  if (K < 2048 && many) return false;
+  if (bits == 4 && N >= 1024 && decode_batch(M, N, K, 1, cus) == 8) return true;
+  return decode_regs_us(M, N, K, bits, cus) < 1.01 * decode_ksplit_us(M, N, K, bits, cus);
 }
 
 // ---------------------------------------------------------------------------

@@ -64,12 +64,15 @@ struct KsplitCall {
   int32_t* acc;
   const int32_t* a_zeros;
   const int32_t* w_sums;
+  int cus;   // compute units
 };
 // Weight layouts: canonical nibbles (any output), the 8-bit activation order
 // (bits 8, y), the decode layout (M <= 16, y or acc).
 constexpr int kWeightsCanonical = 0, kWeightsA8Order = 2, kWeightsDecode = 3;
 // tile: for M > 16, the tile of gemm_rules.h that the dispatch chose.
 hipError_t launch_ksplit(const KsplitCall& c, int bits, int weights, int tile, hipStream_t stream);
+// M <= 16 on the kernel of qgemm_decode.hip.
+hipError_t launch_decode_regs(const KsplitCall& c, int bits, int weights, hipStream_t stream);
 
 // Whether a kernel covers the shape (kGemmAuto and kGemmTile cover all).
 bool gemm_kernel_fits(int kernel, int64_t M, int64_t N, int K, int bits);

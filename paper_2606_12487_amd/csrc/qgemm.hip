@@ -964,7 +964,7 @@ hipError_t launch_t(const uint8_t* a, const float* as, int64_t M, int K,
     case kGemmDecode:
     case kGemmKsplit:
       return launch_ksplit(KsplitCall{a, as, M, K, w, ws, N, ACC_OUT ? nullptr : y, ACC_OUT ? acc : nullptr,
-                                      az, wsum},
+                                      az, wsum, cus},
                            BITS, WA8 ? kWeightsA8Order : kWeightsCanonical, c.tile, stream);
     case kGemmWide:
       launch_wide<BITS, ACC_OUT, WA8, ZP>(a, as, M, K, w, ws, N, y, acc, az, wsum, cus, stream);
@@ -1057,7 +1057,7 @@ hipError_t launch_qlinear_decode_native(const void* codes, const float* a_scales
                                         int bits, const uint8_t* w_dec, const float* w_scales,
                                         int64_t N, void* y, int32_t* out_acc, hipStream_t stream) {
   return launch_ksplit(KsplitCall{static_cast<const uint8_t*>(codes), a_scales, M, K, w_dec, w_scales, N,
-                                  static_cast<__half*>(y), out_acc, nullptr, nullptr},
+                                  static_cast<__half*>(y), out_acc, nullptr, nullptr, device_cus()},
                        bits, kWeightsDecode, -1, stream);
 }
 

@@ -1,5 +1,5 @@
-// W4A4 / W4A8 GEMM for few tokens (gfx950): every decode batch (M <= 16), and
-// larger batches up to several hundred tokens whose 256 x 128 or 192 x 256
+// W4A4 / W4A8 GEMM for few tokens (gfx950): most decode batches (M <= 16; the
+// others run on qgemm_decode.hip), and larger batches up to several hundred tokens whose 256 x 128 or 192 x 256
 // output tiles would leave most compute units idle.  Same product and epilogue
 // as the tile kernels, same bits.
 //
@@ -399,7 +399,7 @@ void launch_tile(int tile, const KsplitCall& c, hipStream_t stream) {
 
 template <int BITS, bool ACC_OUT, bool WA8, bool ZP, bool WDEC>
 void launch_decode(const KsplitCall& c, hipStream_t stream) {
-  const rules::DecodeTile t = rules::decode_tile(c.N, device_cus());
+  const rules::DecodeTile t = rules::decode_tile(c.N, c.cus);
   if (t.ti == 1) launch_cfg<BITS, 1, 1, 8, ACC_OUT, WA8, ZP, WDEC>(c, stream);
   else if (t.waves == 4) launch_cfg<BITS, 2, 1, 4, ACC_OUT, WA8, ZP, WDEC>(c, stream);
   else launch_cfg<BITS, 2, 1, 8, ACC_OUT, WA8, ZP, WDEC>(c, stream);
@@ -416,6 +416,8 @@ void launch_canonical(const KsplitCall& c, int tile, hipStream_t stream) {
 hipError_t launch_ksplit(const KsplitCall& c, int bits, int weights, int tile, hipStream_t stream) {
   if (c.M == 0) return hipSuccess;
   if (c.M > 16 && tile < 0) return hipErrorInvalidValue;
+  if (c.M <= 16 && rules::decode_in_regs(c.M, c.N, c.K, bits, weights == kWeightsDecode, c.cus))
+    return launch_decode_regs(c, bits, weights, stream);
   const bool acc = c.acc != nullptr, zp = c.a_zeros != nullptr;
   if (weights == kWeightsDecode) {
     if (bits == 4) acc ? launch_decode<4, true, false, false, true>(c, stream)

@@ -3,7 +3,8 @@
 //   int8 M N K bits -> the kernel (decode, tile, wide or ksplit), and for ksplit
 //                      its tile as TI x TJ x wavefronts;
 //   fp6 M N K       -> wide, or TI x TJ x wavefronts x stages;
-//   decode N        -> the K-split kernel's workgroup for M <= 16;
+//   decode M N K bits layout (1: decode layout) -> for M <= 16, "regs" with blocks
+//                      x chunks in flight, or "ksplit" with TI x TJ x wavefronts;
 //   tiles           -> every tile of the tables, one a line, then an empty line.
 #include "gemm_rules.h"
 
@@ -38,9 +39,15 @@ int main() {
         std::printf("ksplit %dx%dx%dx%d\n", t.ti, t.tj, t.waves, t.bufs);
       }
     } else if (!std::strcmp(what, "decode")) {
-      if (std::scanf("%ld", &N) != 1) return 1;
-      const DecodeTile t = decode_tile(N, cus);
-      std::printf("%dx1x%d\n", t.ti, t.waves);
+      int layout = 0;
+      if (std::scanf("%ld %ld %d %d %d", &M, &N, &K, &bits, &layout) != 5) return 1;
+      if (decode_in_regs(M, N, K, bits, layout != 0, cus)) {
+        const int blocks = decode_blocks(M, N, bits, cus);
+        std::printf("regs %dx%d\n", blocks, decode_batch(M, N, K, blocks, cus));
+      } else {
+        const DecodeTile t = decode_tile(N, cus);
+        std::printf("ksplit %dx1x%d\n", t.ti, t.waves);
+      }
     } else if (!std::strcmp(what, "tiles")) {
       for (int b = 4; b <= 8; b += 4)
         for (int i = 0; i < ksplit_tiles(b); ++i) {

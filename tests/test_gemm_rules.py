@@ -6,6 +6,9 @@ import subprocess
 
 import pytest
 
+import test_gpu_decode_layout
+import test_gpu_ksplit
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -51,3 +54,30 @@ def test_fp6_shapes_of_the_tile_kernel(routes):
     got = routes(slow + fast)
     assert got[:len(slow)] == ["wide"] * len(slow)
     assert all(r.startswith("ksplit") for r in got[len(slow):]), got
+
+
+def test_decode_shapes_of_the_register_kernel(routes):
+    # Measured 5 to 18% slower on the K-split kernel: short K, and few tokens on the
+    # decode layout; the others up to 1.7 times faster there.
+    regs = ["decode 1 28672 128 4 0", "decode 8 4096 384 8 0", "decode 16 6144 384 4 0",
+            "decode 1 2560 14336 4 1", "decode 2 1024 28672 4 1", "decode 4 28672 4096 4 1",
+            "decode 2 11008 3584 4 1", "decode 1 28672 4096 8 1"]
+    ksplit = ["decode 1 4096 4096 4 0", "decode 16 4096 14336 8 0", "decode 4 16384 128 8 0",
+              "decode 16 8192 8192 4 1", "decode 16 4096 14336 8 1", "decode 1 5120 14336 4 1",
+              "decode 8 57344 8192 4 1"]
+    got = routes(regs + ksplit)
+    assert all(r.startswith("regs") for r in got[:len(regs)]), got
+    assert all(r.startswith("ksplit") for r in got[len(regs):]), got
+
+
+def test_every_decode_kernel_has_a_case(routes):
+    for layout, cases in ((0, test_gpu_ksplit.CASES), (1, test_gpu_decode_layout.CASES)):
+        cases = [c for c in cases if c[0] <= 16]
+        got = routes([f"decode {M} {N} {K} {bits} {layout}" for M, K, N, bits in cases])
+        seen = {(r, c[3]) for r, c in zip(got, cases)}
+        kernels = {"regs 1x4", "regs 2x4", "ksplit 1x1x8", "ksplit 2x1x4", "ksplit 2x1x8"}
+        kernels |= {"regs 1x8"} if layout else set()   # long rows of canonical weights are split
+        assert seen == {(k, bits) for k in kernels for bits in (4, 8)}, layout
+        # two blocks of an odd number, with a last stage of 128 k
+        for r in ("ksplit 2x1x4", "ksplit 2x1x8"):
+            assert any(g == r and c[2] % 32 == 16 and c[1] % 256 == 128 for g, c in zip(got, cases)), (r, layout)

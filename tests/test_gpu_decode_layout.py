@@ -4,8 +4,8 @@ DPTQ_WEIGHTS_DECODE) and of the decode GEMM that reads it
 
 Bar: the layout byte for byte against its definition (written out in numpy);
 the int32 accumulators and fp16 outputs bit for bit against the oracle's exact
-GEMM and pinned epilogue, at one and two 16-channel blocks per workgroup,
-4- and 8-bit activations, M = 1 .. 16.
+GEMM and pinned epilogue, on both kernels at one and two 16-channel blocks per
+workgroup, 4- and 8-bit activations, M = 1 .. 16.
 """
 
 import numpy as np
@@ -43,16 +43,22 @@ def test_decode_layout_bytes(dev, N, K):
     assert np.array_equal(got, decode_layout_ref(w))
 
 
+# Each case runs on one of two kernels, chosen by gemm_rules.h; the routes below are
+# those at 256 compute units, and test_gemm_rules.py keeps every one of them here.
 CASES = [
-    # (M, K, N, bits): the LLaMA-3-8B down decode (K = 14336, N = 4096), LLaMA-2-7B QKV,
-    # a 70B-shaped row count at 8 tokens, small and ragged shapes, and the
-    # two-block workgroups (M * bits >= 64 with N >= 16384)
-    (1, 14336, 4096, 4), (4, 14336, 4096, 8), (16, 14336, 4096, 4), (1, 4096, 12288, 8),
-    (8, 8192, 1024, 4), (3, 256, 16, 8), (7, 1152, 208, 4), (16, 128, 48, 8),
-    (8, 1024, 16384, 8), (16, 1024, 16384, 4), (12, 2048, 16384, 8),
-    # eight chunks in flight per wavefront: exactly 12 chunks per wavefront,
-    # 12 or 13 (a ragged split), and the largest M and grid that take it
-    (1, 12288, 4096, 4), (3, 12416, 2048, 8), (4, 28672, 4096, 4),
+    # (M, K, N, bits).  Weights into registers, blocks of 16 channels x chunks in flight
+    (1, 14336, 4096, 4), (4, 28672, 4096, 4), (1, 12288, 4096, 4),   # 1 x 8: exactly 12 chunks a wavefront, more
+    (2, 12416, 1040, 4), (2, 12416, 2048, 8),                        # 1 x 8: 12 or 13
+    (1, 4096, 12288, 8), (3, 256, 16, 8), (16, 128, 48, 8), (9, 2176, 16400, 8),   # 1 x 4
+    (7, 2944, 2576, 4), (3, 3712, 272, 4), (3, 1152, 2576, 8),       # 1 x 4
+    (16, 128, 57344, 8), (16, 128, 32768, 4),                        # 2 x 4
+    (8, 2944, 16416, 8), (16, 2176, 20512, 4),                       # 2 x 4
+    # K split, as TI x wavefronts; a last stage of 128 k, an odd number of blocks
+    (4, 14336, 4096, 8), (16, 14336, 4096, 4), (8, 8192, 1024, 4),   # 1 x 8
+    (7, 1152, 208, 4), (3, 12416, 2048, 8), (11, 6272, 1040, 4),     # 1 x 8
+    (16, 384, 10256, 4), (16, 1920, 10256, 8), (8, 1152, 8208, 4),   # 2 x 4
+    (8, 1024, 16384, 8), (16, 1024, 16384, 4), (12, 2048, 16384, 8),   # 2 x 4
+    (16, 1152, 4624, 4), (16, 1152, 4624, 8), (5, 640, 4624, 8), (13, 1152, 16400, 8),   # 2 x 8
 ]
 
 

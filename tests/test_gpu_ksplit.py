@@ -23,8 +23,13 @@ dptq = pytest.importorskip("paper_2606_12487_amd")
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (M, K, N, bits).  One block of 16 tokens: the three decode tiles.
-    (1, 128, 16, 4), (5, 640, 4624, 8), (16, 384, 10256, 4), (9, 2176, 16400, 8),
+    # (M, K, N, bits).  At most 16 tokens: one or two blocks of 16 channels on eight
+    # or four wavefronts.
+    (13, 2176, 4128, 8), (9, 2432, 272, 4),                    # 1 x 8
+    (16, 384, 10256, 4), (11, 896, 10256, 8),                  # 2 x 4
+    (5, 640, 4624, 8), (9, 2176, 16400, 8), (3, 640, 4624, 4), (7, 384, 16400, 4),   # 2 x 8
+    # The kernel that streams the weights into registers, at its K; one and two blocks.
+    (1, 128, 16, 4), (13, 384, 272, 8), (3, 384, 3088, 4), (16, 128, 32768, 4), (16, 384, 16416, 8),
     # the tiles of larger batches, as TI x TJ
     (17, 128, 16, 4), (18, 384, 48, 8),            # 1 x 1
     (17, 128, 2064, 4), (31, 640, 2064, 8),        # 1 x 2
