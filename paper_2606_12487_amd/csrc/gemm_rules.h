@@ -125,6 +125,25 @@ inline double tile_kernel_us(int64_t M, int64_t N, int K, int bits, bool wide, i
               : 1.4 + rounds * (4.76 + k * (4.59e-3 + 1.45e-3 * fill));
 }
 
+// What the estimates leave out beyond the shapes they were fitted to.  Below K =
+// 2048: a round's cost besides its k loop (8 bits, N = 6144, K = 256: M = 384 8.7
+// against 6.8 us on the tile kernel).  Beyond M = 1024: the activations' way; the
+// tiles run along M within an XCD, so up to eight L2s read all of them, and each
+// read past the second adds to every element (M = 2853, N = 1456, K = 9216, 8 bits:
+// 89 against 54 us).
+inline double ksplit_extra_us(int tile, int64_t M, int64_t N, int K, int bits, int cus) {
+  const KsplitTile t = ksplit_tile(bits, tile);
+  const int64_t tiles_n = ceil_div(N, 16 * t.ti);
+  double us = 0.0;
+  if (K < 2048) {
+    const int64_t rounds = ceil_div(ceil_div(ceil_div(M, 16 * t.tj) * tiles_n, cus), t.resident);
+    us += (bits == 4 ? 0.4 : 0.65) * (double)(rounds - 1);
+  }
+  if (M > 1024 && tiles_n > 2)
+    us += (bits == 4 ? 5e-8 : 1.2e-7) * (double)((tiles_n < 8 ? tiles_n : 8) - 2) * (double)K * (double)M;
+  return us;
+}
+
 // The kernel of a shape, and the K-split kernel's tile.  M <= 16 streams the
 // weights; otherwise the K-split kernel where its estimate is at least 8% below
 // the tile kernels' (it is the less exact).  At K = 14336, N = 4096, 4 bits it
@@ -138,7 +157,10 @@ inline GemmRoute gemm_route(int64_t M, int64_t N, int K, int bits, int cus) {
   if (M <= 16) return {kGemmDecode, -1};
   const bool wide = wide_is_faster(M, N, K, bits, cus);
   const TilePlan p = ksplit_plan(M, N, K, bits, cus);
-  if (p.tile >= 0 && 1.08 * p.cost < tile_kernel_us(M, N, K, bits, wide, cus)) return {kGemmKsplit, p.tile};
+  if (p.tile >= 0) {
+    const double us = p.cost + ksplit_extra_us(p.tile, M, N, K, bits, cus);
+    if (1.08 * us < tile_kernel_us(M, N, K, bits, wide, cus)) return {kGemmKsplit, p.tile};
+  }
   return {wide ? kGemmWide : kGemmTile, -1};
 }
 

@@ -1,7 +1,7 @@
-// W4A4 / W4A8 GEMM for few tokens (gfx950): most decode batches (M <= 16; the
-// others run on qgemm_decode.hip), and larger batches up to several hundred tokens whose 256 x 128 or 192 x 256
-// output tiles would leave most compute units idle.  Same product and epilogue
-// as the tile kernels, same bits.
+// W4A4 / W4A8 GEMM for few tokens (gfx950): decode batches (M <= 16; some run on
+// qgemm_decode.hip), and larger batches up to several hundred tokens whose 256 x
+// 128 or 192 x 256 output tiles would leave most compute units idle.  Same
+// product and epilogue as the tile kernels, same bits.
 //
 // One workgroup computes a small output tile of 16 TI (n) x 16 TJ (m) and its
 // wavefronts split K between them.  Each wavefront streams its own k range of

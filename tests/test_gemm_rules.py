@@ -41,6 +41,19 @@ def test_every_shape_has_a_kernel(routes):
                        "decode", "ksplit 1x2x8", "wide", "tile", "wide"]
 
 
+def test_shapes_of_the_tile_kernels(routes):
+    # Measured 4 to 65% slower on the K-split kernel: short K, and beyond 1024 rows.
+    slow = ["int8 512 6144 128 4", "int8 256 11008 256 4", "int8 777 4096 256 4", "int8 256 11008 128 8",
+            "int8 160 16384 256 8", "int8 160 11008 128 8", "int8 1024 2576 512 8", "int8 384 6144 512 8",
+            "int8 777 2576 256 8", "int8 512 6144 1024 8", "int8 1536 2576 3584 8", "int8 1536 4096 28672 8",
+            "int8 2853 1456 9216 8", "int8 2174 1184 2944 8", "int8 21 37760 256 8"]
+    fast = ["int8 48 8192 8192 4", "int8 128 6144 4096 8", "int8 333 4096 14336 8", "int8 256 11008 4096 4",
+            "int8 33 4096 1024 8", "int8 100 4096 512 4"]
+    got = routes(slow + fast)
+    assert all(r in ("tile", "wide") for r in got[:len(slow)]), got
+    assert all(r.startswith("ksplit") for r in got[len(slow):]), got
+
+
 def test_fp6_shapes_of_the_tile_kernel(routes):
     # Short K, few channels for many rows, and almost a tile of rows: measured 1.1
     # to 2.3 times slower on the K-split kernel.
