@@ -7,6 +7,7 @@ import subprocess
 import pytest
 
 import test_gpu_decode_layout
+import test_gpu_fp6_ksplit
 import test_gpu_ksplit
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -94,3 +95,16 @@ def test_every_decode_kernel_has_a_case(routes):
         # two blocks of an odd number, with a last stage of 128 k
         for r in ("ksplit 2x1x4", "ksplit 2x1x8"):
             assert any(g == r and c[2] % 32 == 16 and c[1] % 256 == 128 for g, c in zip(got, cases)), (r, layout)
+
+
+def test_every_tile_has_a_case(routes):
+    # A ragged case each: M and N no multiples of the tile, a last stage of 128 k.
+    tiles = {tuple(line.split()) for line in routes(["tiles"]) if line}
+    cases = [c for c in test_gpu_ksplit.CASES if c[0] > 16 and c[0] % 16 and c[2] % 32 and c[1] % 256]
+    got = routes([f"int8 {M} {N} {K} {bits}" for M, K, N, bits in cases])
+    seen = {("int8", str(c[3]), r.split()[1]) for r, c in zip(got, cases) if r.startswith("ksplit")}
+    cases = [c for c in test_gpu_fp6_ksplit.CASES if c[0] % 32]
+    got = routes([f"fp6 {M} {N} {K}" for M, N, K in cases])
+    seen |= {("fp6", "4", r.split()[1]) for r in got if r.startswith("ksplit")}
+    assert seen == tiles, (tiles - seen, seen - tiles)
+    assert "wide" in got

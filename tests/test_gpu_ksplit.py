@@ -2,7 +2,8 @@
 at the shapes where it can go wrong: each of its tiles, ragged M and N
 (remainders of 16-token and of 16-channel blocks), K that is not a multiple of
 256 (a last stage of 128 k, row starts off the 128-byte lines) and K with
-fewer stages than wavefronts.
+fewer stages than wavefronts.  The labels are the dispatch's choice at 256
+compute units; test_gemm_rules.py checks that every tile is among them.
 
 Bar: accumulators and fp16 outputs bit for bit against the oracle's exact GEMM
 and pinned epilogue, for canonical weights, the 8-bit activation order and the
@@ -30,30 +31,25 @@ CASES = [
     (5, 640, 4624, 8), (9, 2176, 16400, 8), (3, 640, 4624, 4), (7, 384, 16400, 4),   # 2 x 8
     # The kernel that streams the weights into registers, at its K; one and two blocks.
     (1, 128, 16, 4), (13, 384, 272, 8), (3, 384, 3088, 4), (16, 128, 32768, 4), (16, 384, 16416, 8),
-    # the tiles of larger batches, as TI x TJ
-    (17, 128, 16, 4), (18, 384, 48, 8),            # 1 x 1
-    (17, 128, 2064, 4), (31, 640, 2064, 8),        # 1 x 2
-    (17, 128, 6160, 4), (47, 896, 4112, 8),        # 2 x 2
-    (33, 640, 6160, 4), (33, 384, 6160, 8),        # 2 x 3
-    (63, 384, 6160, 4), (17, 640, 11024, 8),       # 4 x 2
-    (129, 384, 4112, 4), (129, 384, 4112, 8),      # 4 x 3
-    (300, 128, 3088, 4), (300, 128, 3088, 8),      # 4 x 4
-    (161, 896, 6160, 4), (161, 2432, 6160, 8),     # 4 x 6
-    (97, 384, 11024, 4), (97, 384, 11024, 8),      # 6 x 4
-    (129, 1408, 11024, 8),                         # 6 x 6
-    (161, 896, 8208, 8),                           # 8 x 4
-    # four wavefronts (the stage refilled part by part from eight blocks on,
-    # but for 4 x 4 at 4 bits)
-    (18, 1152, 8608, 4), (20, 256, 8800, 8),       # 2 x 2, 4 x 2
-    (17, 1152, 8704, 8),                           # 4 x 2, one to two stages a wavefront
-    (33, 896, 9072, 4),                            # 2 x 3
-    (52, 1152, 12304, 4), (33, 1152, 4256, 8),     # 2 x 4
-    (50, 2944, 4112, 4),                           # 2 x 4 on eight
-    (512, 1408, 3728, 4), (50, 2432, 8224, 8),     # 4 x 4
-    (65, 1408, 12480, 8),                          # 4 x 6
-    (97, 1920, 12960, 8),                          # 4 x 8
-    (163, 2176, 8272, 8),                          # 8 x 4
-    (99, 4992, 12416, 4), (146, 6272, 8448, 4),    # 4 x 8, 8 x 4
+    # The tiles of larger batches, as TI x TJ x wavefronts.
+    (17, 128, 16, 4), (18, 384, 48, 8), (17, 128, 2064, 4), (17, 128, 6160, 4),  # 1 x 1 x 8
+    (31, 640, 2064, 8), (17, 2432, 2448, 4),                # 1 x 2 x 8
+    (18, 384, 7088, 4), (18, 384, 6416, 8),                 # 2 x 2 x 8
+    (33, 1920, 4240, 4), (33, 1920, 4240, 8),               # 2 x 3 x 8
+    (50, 2944, 4112, 4),                                    # 2 x 4 x 8
+    (33, 2688, 8560, 4), (37, 896, 8496, 8),                # 4 x 3 x 8
+    (33, 640, 6160, 4), (63, 384, 6160, 4), (129, 384, 4112, 4), (300, 128, 3088, 4),  # 2 x 2 x 4
+    (161, 896, 6160, 4), (97, 384, 11024, 4), (18, 1152, 8608, 4),
+    (33, 896, 9072, 4),                                     # 2 x 3 x 4
+    (47, 896, 4112, 8), (33, 384, 6160, 8), (129, 384, 4112, 8), (97, 384, 11024, 8),  # 2 x 4 x 4
+    (161, 896, 8208, 8), (52, 1152, 12304, 4), (33, 1152, 4256, 8),
+    (512, 1408, 3728, 4), (50, 2432, 8224, 8), (299, 1408, 6416, 4), (49, 2176, 10288, 8),  # 4 x 4 x 4
+    (163, 2176, 8272, 8), (146, 6272, 8448, 4), (149, 6272, 8496, 4),  # 8 x 4 x 4
+    (97, 1920, 12960, 8), (97, 1920, 12848, 8),             # 4 x 8 x 4
+    (99, 4992, 12416, 4), (98, 4992, 12432, 4),
+    (17, 640, 11024, 8), (300, 128, 3088, 8), (129, 1408, 11024, 8), (20, 256, 8800, 8),  # 4 x 2 x 4
+    (17, 1152, 8704, 8),
+    (161, 2432, 6160, 8), (65, 1408, 12480, 8),             # 4 x 6 x 4
 ]
 
 
