@@ -252,7 +252,8 @@ inline double decode_ksplit_us(int64_t M, int64_t N, int K, int bits, int cus) {
 
 // Which of the two.  Where a wavefront has at most half a chunk the way through
 // LDS only adds latency: K <= 128, or K <= 512 on at most two blocks of channels
-// a compute unit (M = 1, N = 4096, K = 512, 8 bits: 2.75 against 2.99 us); but
+// a compute unit (M = 1, N = 4096, K = 512, 8 bits: 2.75 against 2.99 us), or K <=
+// 384 on more than four at 8 bits (M = 4, N = 20480, K = 256: 4.4 against 5.1); but
 // three of the register kernel's workgroups fit a compute unit at 8 bits, so
 // between three and four blocks it loses a round (M = 4, N = 14336, K = 128: 3.4
 // against 3.1 us).  Longer rows of canonical weights take the K-split kernel,
@@ -269,7 +270,8 @@ inline bool decode_in_regs(int64_t M, int64_t N, int K, int bits, bool decode_la
   const bool many = nb > 2 * (int64_t)cus;
   if (K <= 128) return !(bits == 8 && nb > 3 * (int64_t)cus && nb <= 4 * (int64_t)cus);
   if (K <= 512 && !many) return true;
-  if (!decode_layout) return bits == 8 && K <= 384 && nb > 4 * (int64_t)cus;
+  if (bits == 8 && K <= 384 && nb > 4 * (int64_t)cus) return true;
+  if (!decode_layout) return false;
   if (K < 2048 && many) return false;
   if (bits == 4 && N >= 1024 && decode_batch(M, N, K, 1, cus) == 8) return true;
   return decode_regs_us(M, N, K, bits, cus) < 1.01 * decode_ksplit_us(M, N, K, bits, cus);

@@ -75,7 +75,8 @@ def test_decode_shapes_of_the_register_kernel(routes):
     # decode layout; the others up to 1.7 times faster there.
     regs = ["decode 1 28672 128 4 0", "decode 8 4096 384 8 0", "decode 16 6144 384 4 0",
             "decode 1 2560 14336 4 1", "decode 2 1024 28672 4 1", "decode 4 28672 4096 4 1",
-            "decode 2 11008 3584 4 1", "decode 1 28672 4096 8 1"]
+            "decode 2 11008 3584 4 1", "decode 1 28672 4096 8 1",
+            "decode 4 20480 256 8 1"]
     ksplit = ["decode 1 4096 4096 4 0", "decode 16 4096 14336 8 0", "decode 4 16384 128 8 0",
               "decode 16 8192 8192 4 1", "decode 16 4096 14336 8 1", "decode 1 5120 14336 4 1",
               "decode 8 57344 8192 4 1"]
