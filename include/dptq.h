@@ -196,10 +196,10 @@ typedef enum {
  * loads are in flight, then streams its weight slice against them: no second
  * launch, and the GEMM never reads the codes back from HBM (workgroup 0 still
  * stores them).  The rotation is repeated in every workgroup, so this path
- * wins only for one or two rows of moderate K; DPTQ_DECODE_AUTO takes it for
- * N <= 16384 and either M = 1 with K <= 16384 and had_size a power of two
- * <= 8192, or M = 2 with K <= 12288 and had_size a power of two <= 4096; and
- * the two launches otherwise (had_size = 28 * 2^j included).
+ * wins only for one or two rows; DPTQ_DECODE_AUTO takes it where it measured the
+ * faster: had_size a power of two and, on 256 compute units, M = 1 with N at most
+ * 4096 (K > 12288) to 16384 (K from 8192, or 4096), or M = 2 with N at most 4096 to
+ * 12288 (K <= 4096); and the two launches otherwise (had_size = 28 * 2^j included).
  *
  *   x, M, K, had_size, bits   as for dptq_rotate_quant; 1 <= M <= 16 (M = 0
  *            enqueues nothing), K a multiple of 128

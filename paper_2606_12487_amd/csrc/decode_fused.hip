@@ -1,15 +1,14 @@
 // Decode-shape quantized linear in one launch: rotate + quantize the M <= 16
 // token rows and the weight-streaming GEMM with its dequant epilogue.
 //
-// The grid is the decode GEMM's: one workgroup of 512 threads per 16 output
-// channels, whose 8 wavefronts split K.  Each workgroup starts the loads of
-// its first weight chunks, rotates and quantizes all M rows itself into LDS,
-// and runs the GEMM with the codes read from LDS.  The rotation is the
-// rotate+quantize kernels' arithmetic: the row widened to fp32, butterflies
-// over index bits 0, 1, 2, ... in that order, then for h = 28 * 2^j the dense
-// 28-point stage summed sequentially over the slow index; the scale is
-// fl32(absmax / qmax) and the codes are the correctly rounded quotients
-// rounded half to even.  Every workgroup repeats the rotation of the few
+// One workgroup of 512 threads per 16 output channels, whose 8 wavefronts split
+// K.  Each workgroup starts the loads of its first weight chunks, rotates and
+// quantizes all M rows itself into LDS, and runs the GEMM with the codes read
+// from LDS.  The rotation is the rotate+quantize kernels' arithmetic: the row
+// widened to fp32, butterflies over index bits 0, 1, 2, ... in that order, then
+// for h = 28 * 2^j the dense 28-point stage summed sequentially over the slow
+// index; the scale is fl32(absmax / qmax) and the codes are the correctly rounded
+// quotients rounded half to even.  Every workgroup repeats the rotation of the few
 // decode rows; that costs less than a second launch and a round trip of the
 // codes through HBM, and no workgroup ever waits for another.  Workgroup 0
 // also stores the codes and scales when the caller asks for them.
@@ -324,25 +323,14 @@ int64_t decode_fused_lds(int64_t M, int K, HadSplit hs, int bits) {
   return code_rows_bytes(M, K, bits) + staging_bytes(K);
 }
 
-// Measured on decode shapes: the repeated rotation costs less than the
-// second launch for one row of K <= 16384 with h = 2^j <= 8192, and for two
-// rows of K <= 12288 with h = 2^j <= 4096; in every case for at most 1024
-// workgroups (about three per compute unit, so each rotates once).  More
-// rows, longer rows or more workgroups make it the slower path, and so does
-// h = 28 * 2^j since the two-launch rotation got faster (15.1 against
-// 15.7 us for one row of 14336, h = 28 x 512, N = 4096).
-bool decode_one_launch_wins(int64_t M, int K, HadSplit hs, int bits, int64_t N) {
-  if (N > 16384 || decode_fused_lds(M, K, hs, bits) > kFusedLdsMax) return false;
-  if (M == 1) return hs.f == 1 && hs.j <= 13 && K <= 16384;
-  return M == 2 && hs.f == 1 && hs.j <= 12 && K <= 12288;
-}
-
 hipError_t launch_decode_fused(const void* x, int64_t M, int K, HadSplit hs, int bits,
                                const uint8_t* w_packed, const float* w_scales, int64_t N, void* y,
                                void* codes, float* a_scales, int mode, hipStream_t stream) {
   if (M == 0) return hipSuccess;
   if (mode == kDecodeAuto)
-    mode = decode_one_launch_wins(M, K, hs, bits, N) ? kDecodeOneLaunch : kDecodeTwoLaunches;
+    mode = decode_fused_lds(M, K, hs, bits) <= kFusedLdsMax && rules::decode_one_launch(M, K, hs.f, hs.j, N, device_cus())
+               ? kDecodeOneLaunch
+               : kDecodeTwoLaunches;
   if (mode == kDecodeTwoLaunches) {
     hipError_t e = launch_rotate_quant_f16(x, M, K, hs, bits, codes, a_scales, stream);
     if (e != hipSuccess) return e;

@@ -277,6 +277,30 @@ inline bool decode_in_regs(int64_t M, int64_t N, int K, int bits, bool decode_la
   return decode_regs_us(M, N, K, bits, cus) < 1.01 * decode_ksplit_us(M, N, K, bits, cus);
 }
 
+// Whether the one-launch decode (decode_fused.hip), every workgroup of 16
+// channels repeating the rotation of the M rows, beats rotate + quantize and then
+// the decode GEMM, for h = f * 2^j.  Measured over 1400 shapes (K 512-20480, N
+// 1024-24576, 4 and 8 bits alike, weights cycling through 768 MB), one launch
+// against two: M = 1, N = 4096, K = 4096 0.68 of the time, K = 14336 0.74; N =
+// 12288, K = 4096 0.82, K = 8192 0.83, K = 2048 0.98, K = 14336 1.22; N = 16384, K =
+// 12288 0.90, K = 4096 (one whole segment) 0.87-0.94, K = 5120 1.02.  M = 2, N = 4096 0.74 at K = 4096, 0.91 at 12288;
+// N = 12288 0.92 at K = 4096, 1.4 at 12288.  Above K = 12288 a workgroup's staging
+// leaves room for one a compute unit.  More rows never gained over 5%, and h = 28 *
+// 2^j is slower throughout (the 28-point stage in every workgroup): 1.04-4.
+inline bool decode_one_launch(int64_t M, int K, int f, int j, int64_t N, int cus) {
+  if (f != 1 || M > 2) return false;
+  const int64_t nb = N / 16;   // workgroups
+  int per_cu;
+  if (M == 1) {
+    if (j > 14) return false;
+    per_cu = K > 12288 ? 1 : K < 2048 ? 2 : j < 13 && (K >= 8192 || (K > 3072 && K <= 4096)) ? 4 : 3;
+  } else {
+    if (j > 12 || K > 12288) return false;
+    per_cu = K > 4096 || K < 2048 ? 1 : K < 2560 ? 2 : 3;
+  }
+  return nb <= (int64_t)per_cu * cus;
+}
+
 // ---------------------------------------------------------------------------
 // K-split FP6 GEMM.  Tiles as above in blocks of 32, with the stages a wavefront
 // keeps.  Fitted to 217 shapes (M 64-2048, N 1024-28672, K 2048-28672; weights

@@ -115,10 +115,9 @@ int64_t decode_fused_lds(int64_t M, int K, HadSplit hs, int bits);
 // launch, every workgroup rotating the M rows itself (requires
 // decode_fused_lds(M, K, hs, bits) <= kFusedLdsMax); mode 2: the
 // rotate+quantize kernel then the decode GEMM; mode 0: the one launch where
-// it is the faster (decode_one_launch_wins).  codes / a_scales receive the
+// it is the faster (decode_one_launch in gemm_rules.h).  codes / a_scales receive the
 // activation codes and scales (both always written).
 constexpr int kDecodeAuto = 0, kDecodeOneLaunch = 1, kDecodeTwoLaunches = 2;
-bool decode_one_launch_wins(int64_t M, int K, HadSplit hs, int bits, int64_t N);
 hipError_t launch_decode_fused(const void* x, int64_t M, int K, HadSplit hs, int bits,
                                const uint8_t* w_packed, const float* w_scales, int64_t N, void* y,
                                void* codes, float* a_scales, int mode, hipStream_t stream);
