@@ -1,4 +1,4 @@
-// Which GEMM kernel and tile a shape runs: pure functions of the sizes and the
+// Which kernel and tile a shape runs: pure functions of the sizes and the
 // compute units, evaluated once per call (host only, no HIP, so that they can be
 // checked without a GPU).  Estimates are in microseconds; the kernels that they
 // choose between return the same bits.
@@ -361,6 +361,21 @@ inline int fp6_ksplit_or_none(int64_t M, int64_t N, int K, int cus) {
     if (reads > 2) p.cost += 6e-8 * k * (double)M * (double)(reads - 2);
   }
   return p.cost < (fits ? 0.95 : 0.9) * cost ? p.tile : -1;
+}
+
+// ---------------------------------------------------------------------------
+// Rotate + quantize: whether rows of one block of 28 * 2^j (j = 9, 10; fp16 in,
+// codes out) stay in registers (rq28_kernel) or go to the general kernel.  More
+// than 64 rows of 28 x 512 (256 rows 7.2 us, against 9.8 us on the general
+// kernel's 256 threads a row; its 1024 threads for fewer rows are as fast, 6.6 and
+// 6.7 us), and more rows than compute units of 28 x 1024 (256 rows 11.3 us against
+// 10.6 us, 300 rows 17.9 us against 19.0 us).  A launch holds less than 2^32
+// threads; rows whose 1024 threads are more keep to the general kernel.
+// ---------------------------------------------------------------------------
+constexpr int kRq28Threads = 1024;
+inline bool rotate_in_registers(int64_t M, int K, int f, int j, int cus) {
+  if (f != 28 || K != (28 << j) || (M + 31) * kRq28Threads > 0xFFFFFFFFll) return false;
+  return (j == 9 && M > 64) || (j == 10 && M > cus);
 }
 
 }  // namespace rules

@@ -1089,18 +1089,11 @@ rq28_kernel(const __half* __restrict__ x, int M, const uint8_t* __restrict__ sig
 template <int BITS, int J, int WAVES, int HALVES, bool FP6>
 hipError_t launch_rq28_t(const __half* x, int64_t M, const uint8_t* signs, uint8_t* codes, float* scales,
                          hipStream_t stream) {
+  static_assert(WAVES * 64 == rules::kRq28Threads, "the rule bounds the launch by these");
   const int64_t grid = FP6 ? (M + 31) / 32 * 32 : M;
   hipLaunchKernelGGL((rq28_kernel<BITS, J, WAVES, HALVES, FP6>), dim3((unsigned)grid), dim3(WAVES * 64), 0,
                      stream, x, (int)M, signs, codes, scales);
   return hipGetLastError();
-}
-
-// Rows it takes: more than 64 of 28 x 512 (256 rows 7.2 us, against 9.8 us on
-// the general kernel's 256 threads a row; its 1024 threads for fewer rows are as
-// fast, 6.6 and 6.7 us), and more rows than compute units of 28 x 1024 (256 rows
-// 11.3 us against 10.6 us, 300 rows 17.9 us against 19.0 us).
-bool use_rq28(int64_t M, int K, HadSplit hs) {
-  return hs.f == 28 && K == (28 << hs.j) && ((hs.j == 9 && M > kFewRows) || (hs.j == 10 && M > device_cus()));
 }
 
 template <int BITS, bool FP6>
@@ -1188,7 +1181,7 @@ hipError_t launch_rq(const Tin* x, int64_t M, int K, HadSplit hs, uint8_t* codes
     }
   }
   if constexpr (!WEIGHT && !STATS && sizeof(Tin) == 2) {
-    if (use_rq28(M, K, hs))
+    if (rules::rotate_in_registers(M, K, hs.f, hs.j, device_cus()))
       return launch_rq28<BITS, FP6>(reinterpret_cast<const __half*>(x), M, hs.j, signs, codes, scales, stream);
   }
   if (hs.f == 28)

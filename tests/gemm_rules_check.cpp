@@ -6,6 +6,7 @@
 //   decode M N K bits layout (1: decode layout) -> for M <= 16, "regs" with blocks
 //                      x chunks in flight, or "ksplit" with TI x TJ x wavefronts;
 //   fused M K f j N -> "one" or "two" launches for h = f * 2^j;
+//   rotate M K f j  -> "registers" or "general" for h = f * 2^j;
 //   tiles           -> every tile of the tables, one a line, then an empty line.
 #include "gemm_rules.h"
 
@@ -53,6 +54,10 @@ int main() {
       int f = 0, j = 0;
       if (std::scanf("%ld %d %d %d %ld", &M, &K, &f, &j, &N) != 5) return 1;
       std::printf("%s\n", decode_one_launch(M, K, f, j, N, cus) ? "one" : "two");
+    } else if (!std::strcmp(what, "rotate")) {
+      int f = 0, j = 0;
+      if (std::scanf("%ld %d %d %d", &M, &K, &f, &j) != 4) return 1;
+      std::printf("%s\n", rotate_in_registers(M, K, f, j, cus) ? "registers" : "general");
     } else if (!std::strcmp(what, "tiles")) {
       for (int b = 4; b <= 8; b += 4)
         for (int i = 0; i < ksplit_tiles(b); ++i) {

@@ -94,6 +94,15 @@ def test_one_launch_where_it_is_the_faster(routes):
     assert routes(one + two) == ["one"] * len(one) + ["two"] * len(two)
 
 
+def test_rotation_launches_hold_less_than_2_32_threads(routes):
+    # 1024 threads a row in registers, 256 on the general kernel at 28 x 512.
+    assert routes(["rotate 65 14336 28 9", "rotate 64 14336 28 9", "rotate 257 28672 28 10", "rotate 256 28672 28 10",
+                   "rotate 4194272 14336 28 9", "rotate 4194273 14336 28 9", "rotate 5000000 14336 28 9",
+                   "rotate 4096 28672 28 9", "rotate 4096 16384 1 14"]) == [
+                       "registers", "general", "registers", "general", "registers", "general", "general",
+                       "general", "general"]
+
+
 def test_every_decode_kernel_has_a_case(routes):
     for layout, cases in ((0, test_gpu_ksplit.CASES), (1, test_gpu_decode_layout.CASES)):
         cases = [c for c in cases if c[0] <= 16]
