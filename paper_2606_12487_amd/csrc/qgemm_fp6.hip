@@ -260,7 +260,7 @@ __device__ __forceinline__ void qgemm_fp6_body(const uint8_t* __restrict__ a6,
         const int b = qq / 3;
         const int rb = isa ? min(rba + b, mblk - 1) : min(rbw + b, nblk - 1);
         const uint8_t* src = (isa ? a6 + (size_t)kb * astride : w6 + (size_t)kb * wstride) +
-                             (uint32_t)(rb * kF6Block + (qq - 3 * b) * 1024);
+                             (size_t)rb * kF6Block + (qq - 3 * b) * 1024;
         f6_dma16(src, lane16, base + q * 1024);
       }
     }

@@ -64,3 +64,19 @@ def test_fp6_ksplit_scales_off_16_bytes(off):
     y = dptq.qlinear_fp6(a6, a_s[off:], w6, w_s[off:], M, K, N)
     ref = dptq.qlinear_fp6(a6, a_s[off:].clone(), w6, w_s[off:].clone(), M, K, N)
     assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
+
+
+def test_fp6_rows_beyond_4_gib():
+    # 32-row blocks whose byte offset is past 2^32 (3072 bytes each), on a shape
+    # of the 192 x 256 kernel's clamped variant; the last rows against the int8 GEMM.
+    M, N, K = (2 ** 32 // 3072 + 8) * 32, 16, 128
+    g = torch.Generator(device="cuda")
+    g.manual_seed(4)
+    a = torch.randint(0, 256, (M, K // 2), generator=g, device="cuda", dtype=torch.uint8)
+    w = torch.randint(0, 256, (N, K // 2), generator=g, device="cuda", dtype=torch.uint8)
+    a_s = torch.rand((M,), generator=g, device="cuda")
+    w_s = torch.rand((N,), generator=g, device="cuda") * 1e-3
+    y = dptq.qlinear_fp6(dptq.pack_fp6(a), a_s, dptq.pack_fp6(w), w_s, M, K, N)
+    for rows in (slice(0, 512), slice(M - 512, M)):
+        ref = dptq.qlinear(a[rows], a_s[rows], 4, w, w_s)
+        assert torch.equal(y[rows].view(torch.int16), ref.view(torch.int16)), rows
