@@ -16,19 +16,19 @@ dptq = pytest.importorskip("paper_2606_12487_amd")
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # (M, N, K)              blocks of 32 (n x m), wavefronts
-    (10, 32, 128),         # 1 x 1, 8: seven wavefronts without a k block
-    (33, 1040, 1152),      # 1 x 1, 8: N % 32 == 16, 9 k blocks
-    (34, 5344, 128),       # 1 x 2, 8
-    (99, 5328, 1920),      # 1 x 2, 8
-    (68, 9744, 128),       # 2 x 2, 4, several workgroups a compute unit
+    # (M, N, K)              blocks of 32 (n x m), wavefronts, stages each
+    (10, 32, 128),         # 1 x 1, 8, 2: seven wavefronts without a k block
+    (33, 1040, 1152),      # 1 x 1, 8, 2: N % 32 == 16, 9 k blocks
+    (34, 5344, 128),       # 1 x 2, 8, 2
+    (68, 9744, 128),       # 2 x 2, 4, 1: several workgroups a compute unit
     (1023, 2320, 1152),    # the same, ragged
-    (8, 9680, 128),        # 2 x 2, 4, two stages in flight
+    (8, 9680, 128),        # 2 x 2, 4, 2
+    (99, 5328, 1920),      # the same, 15 k blocks
+    (68, 8336, 384),       # 2 x 3, 4, 2
     (500, 2064, 2176),     # the same, 17 k blocks
-    (68, 8336, 384),       # 2 x 3, 4
-    (98, 8464, 1920),      # 2 x 4, 4
-    (258, 10016, 1408),    # 4 x 3, 4
-    (331, 8416, 2048),     # 4 x 4, 4: the sum takes several passes
+    (98, 8464, 1920),      # 2 x 4, 4, 2
+    (258, 10016, 1408),    # 4 x 3, 4, 1
+    (331, 8416, 2048),     # 4 x 4, 4, 1: the sum takes several passes
     (517, 10928, 384),     # the 192 x 256 kernel at its fewest stages
     # its clamped variant: one and two stages, too few rows, too few channels
     (777, 11024, 128), (1029, 6160, 256), (217, 28688, 384), (65569, 160, 128),
@@ -53,17 +53,18 @@ def test_fp6_ksplit_tiles(M, N, K):
 
 @pytest.mark.parametrize("off", [1, 2, 3])
 def test_fp6_ksplit_scales_off_16_bytes(off):
-    # The scales may start at any multiple of 4 bytes.
+    # The entry point takes scales that start at any multiple of 4 bytes.
     M, N, K = 500, 2064, 256
     rng = np.random.default_rng(off)
     a = workloads.random_weight_bytes(rng, M, K)
     w = workloads.random_weight_bytes(rng, N, K)
     a6, w6 = (dptq.pack_fp6(torch.from_numpy(v).cuda()) for v in (a, w))
-    a_s = torch.from_numpy(workloads.random_scales(rng, M + off, 1e-3, 1.0)).cuda()
-    w_s = torch.from_numpy(workloads.random_scales(rng, N + off, 1e-5, 1e-4)).cuda()
-    y = dptq.qlinear_fp6(a6, a_s[off:], w6, w_s[off:], M, K, N)
-    ref = dptq.qlinear_fp6(a6, a_s[off:].clone(), w6, w_s[off:].clone(), M, K, N)
-    assert torch.equal(y.view(torch.int16), ref.view(torch.int16))
+    a_s = workloads.random_scales(rng, M, 1e-3, 1.0)
+    w_s = safe_w_scales(rng, N, K, a_s, 4)
+    ad, wd = (torch.from_numpy(np.concatenate([np.full(off, np.nan, np.float32), v])).cuda()[off:] for v in (a_s, w_s))
+    y = dptq.qlinear_fp6(a6, ad, w6, wd, M, K, N).cpu().numpy()
+    ref = oracle_y(qlinear_acc_ref(a, 4, w), a_s, w_s)
+    assert np.array_equal(y.view(np.uint16), ref.view(np.uint16))
 
 
 def test_fp6_rows_beyond_4_gib():
