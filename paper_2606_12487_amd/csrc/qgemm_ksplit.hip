@@ -15,7 +15,9 @@
 // registers puts consecutive lanes in different rows: measured 16 bytes per
 // clock and compute unit.  A direct global->LDS load whose consecutive lanes
 // cover 64 bytes of a row reached about 29, and whole 128-byte lines (256 k of
-// a 4-bit row at a time; half lines are fetched twice) about 40 to 50.
+// a 4-bit row at a time; half lines are fetched twice) about 40 to 50, in the k
+// loop and with the operands in the caches; whole launches with the weights from
+// memory, start and sums included, 24 on long rows (19.6 us for this shape).
 // M = 128, K = 14336, N = 4096 at 8 bits (32 x 64 tiles, 256 workgroups):
 // 27.5 us, 17.0 us and 13.8 us for the three, against 75 us for the 256 x 128
 // tile kernel on its 16 workgroups.
@@ -252,9 +254,10 @@ qgemm_ksplit(const uint8_t* __restrict__ a_codes, const float* __restrict__ a_sc
       }
     }
   }
-  // Larger tiles: the stage is refilled part by part (the weights and the first activation block, then each of the other
-  // blocks), each part as soon as its reads have returned, and a part is read
-  // while the MFMAs of the one before run; so loads leave all the time.
+  // Larger tiles: the stage is refilled part by part (the weights and the first
+  // activation block, then each of the other blocks), each part as soon as its
+  // reads have returned, and a part is read while the MFMAs of the one before
+  // run; so loads leave all the time.
   // Step j of stage s reads part j + 1 of it (the last step part 0 of stage
   // s + 1); more: whether stage s + 1 exists.
   constexpr int kP0 = 2 * TI + kAB;   // loads of part 0

@@ -9,11 +9,13 @@
 // reduced across the workgroup, and the final pass divides, rounds to nearest
 // even, packs and stores the codes with coalesced writes.
 //
-// Two kernels: a register-phase kernel for power-of-two sizes up to 4096 (the
-// sizes of every LLaMA projection except the largest ones), and a general
-// kernel for the others (28 * 2^j, and 2^j above 4096).  Both are limited by
-// vector ALU issue, not by memory: the fp32 butterflies alone are log2(h)
-// instructions per element, and packed fp32 arithmetic is not used.
+// Four kernels: a register-phase kernel for power-of-two sizes up to 4096 (the
+// sizes of every LLaMA projection except the largest ones), one that keeps many
+// rows of one 28 * 512 or 28 * 1024 block in registers, a segmented one for many
+// rows at h = 16384, and a general kernel for the others (28 * 2^j, and 2^j above
+// 4096).  They are limited by vector ALU issue, not by memory: the fp32
+// butterflies alone are log2(h) instructions per element, and packed fp32
+// arithmetic is not used.
 //
 // Quotient: t = fl32(y / s) is formed as q = y * r, e = fma(-q, s, y),
 // t = fma(e, r, q) with r = fl32(1 / s) (Markstein's correction, one
@@ -829,8 +831,8 @@ rq_seg_kernel(const __half* __restrict__ x, int M, int K, int J, uint8_t* __rest
 // a compute unit and one's loads, barriers and stores run beside the other's
 // arithmetic (the general kernel holds one row of 28 x 1024).
 //
-// What bounds it: the vector ALU, about 25 operations an element, and the fp32
-// MFMAs, whose cycles add up (counters, 4096 x 28672: 192 and 115 of 354 thousand
+// What bounds it: the vector ALU, 28 instructions an element, and the fp32 MFMAs,
+// whose cycles add up (counters, 4096 x 28672 into FP6: 202 and 115 of 350 thousand
 // cycles a SIMD).  4096 x 14336 at 8 bits 84.2 -> 64.0 us (2.75 TB/s), 4096 x
 // 28672 158.7 -> 124-129 us, with the FP6 output 186.1 -> 137-142 us; eight wavefronts a row
 // instead of sixteen 127.7 and 139.7 us.
