@@ -43,9 +43,12 @@ PEAK_LANE_OPS = 256 * 4 * 16 * 2.4e9
 METRIC = "W4A4/W4A8 qlinear TOPS (rotate+quant+GEMM), % int8 MFMA peak; decode GB/s"
 HEADLINE = "llama2_70b_layer"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_qgemm_fp6_llama2_70b_stack.txt")
-TRAFFIC_SOURCE = os.path.join(ROOT, "paper_2606_12487_amd", "csrc", "qgemm_fp6.hip")
+# The sources of the kernels that a summary describes, and of the rule that picks them.
+_CSRC = os.path.join(ROOT, "paper_2606_12487_amd", "csrc")
+TRAFFIC_SOURCE = tuple(os.path.join(_CSRC, f) for f in ("qgemm_fp6.hip", "fp6_device.h"))
 DECODE_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_qgemm_decode_llama2_70b_M8.txt")
-DECODE_TRAFFIC_SOURCE = os.path.join(ROOT, "paper_2606_12487_amd", "csrc", "qgemm.hip")
+DECODE_TRAFFIC_SOURCE = tuple(os.path.join(_CSRC, f) for f in (
+    "qgemm_ksplit.hip", "qgemm_decode.hip", "qgemm_device.h", "gemm_rules.h"))
 
 
 def parse():
@@ -74,9 +77,9 @@ def progress(msg):
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def source_digest(path):
+def source_digest(paths):
     import hashlib
-    return hashlib.sha256(open(path, "rb").read()).hexdigest()[:16]
+    return hashlib.sha256(b"".join(open(p, "rb").read() for p in paths)).hexdigest()[:16]
 
 
 def measured_traffic(path=None, source=None, key="hbm_bytes_per_launch"):

@@ -2,7 +2,7 @@
 
     python -m paper_2606_12487_amd.rocprof_summary stats STATS_CSV [--top N] [--title T] [--command C]
     python -m paper_2606_12487_amd.rocprof_summary traffic FETCH_CSV WRITE_CSV \
-        COPY_FETCH_CSV COPY_WRITE_CSV --kernel SUBSTR --source FILE \
+        COPY_FETCH_CSV COPY_WRITE_CSV --kernel SUBSTR --source FILE [FILE ...] \
         --algorithmic-bytes B [--reduce mean|median] [--title T] [--command C]
     python -m paper_2606_12487_amd.rocprof_summary trace TRACE_CSV --kernel SUBSTR \
         --first N [--labels a,b,c] [--bytes B1,B2,B3] [--title T] [--command C]
@@ -14,7 +14,8 @@
 counter runs of a kernel (FETCH_SIZE, WRITE_SIZE: KiB per dispatch) and the
 same counters for a device copy of 256 MiB, scales the kernel's figures by
 known-bytes / counted-bytes of the copy, and prints HBM bytes per launch
-together with the kernel source digest they belong to.  `trace` reads the
+together with the digest of the kernel sources they belong to.  A kernel is
+named by a part of its name, or by several separated by `|`.  `trace` reads the
 per-dispatch kernel trace and prints the mean duration of one kernel over its
 first N dispatches (a benchmark's headline launches, which come first) and
 over all of them; with --labels, the dispatches of a kernel launched at
@@ -60,9 +61,13 @@ def stats(path, title, command, top=0):
     return "\n".join(out)
 
 
+def _is(name, kernel):
+    return any(k in name for k in kernel.split("|"))
+
+
 def _counter(path, counter, kernel, reduce="median"):
     vals = [float(r["Counter_Value"]) for r in _rows(path)
-            if r["Counter_Name"] == counter and kernel in r["Kernel_Name"]]
+            if r["Counter_Name"] == counter and _is(r["Kernel_Name"], kernel)]
     if not vals:
         raise SystemExit(f"no {counter} rows for kernels matching {kernel!r} in {path}")
     f = statistics.mean if reduce == "mean" else statistics.median
@@ -70,7 +75,7 @@ def _counter(path, counter, kernel, reduce="median"):
 
 
 def trace(path, kernel, first, title, command, labels=None, nbytes=None):
-    rows = [r for r in _rows(path) if kernel in r["Kernel_Name"]]
+    rows = [r for r in _rows(path) if _is(r["Kernel_Name"], kernel)]
     if not rows:
         raise SystemExit(f"no dispatches of kernels matching {kernel!r} in {path}")
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
@@ -106,14 +111,14 @@ def traffic(a, title, command):
     wscale = COPY_BYTES / (cwrite * 1024.0)
     fb = fetch * 1024.0 * fscale
     wb = write * 1024.0 * wscale
-    digest = hashlib.sha256(open(a.source, "rb").read()).hexdigest()[:16]
+    digest = hashlib.sha256(b"".join(open(f, "rb").read() for f in a.source)).hexdigest()[:16]
     out = [f"# {title}" if title else "# HBM traffic per launch"]
     if command:
         for c in command.split(" ;; "):
             out.append(f"# command: {c}")
     out += [
         f"kernel: {a.kernel}",
-        f"source: {a.source.split('/')[-1]}",
+        f"source: {' '.join(f.split('/')[-1] for f in a.source)}",
         f"source_sha256_16: {digest}",
         f"dispatches_fetch: {nf}",
         f"dispatches_write: {nw}",
@@ -136,7 +141,7 @@ def counters(paths, kernel, labels, skip, title, command):
     per = {}   # counter -> dispatch id -> summed value
     for path in paths:
         for r in _rows(path):
-            if kernel in r["Kernel_Name"]:
+            if _is(r["Kernel_Name"], kernel):
                 d = per.setdefault(r["Counter_Name"], {})
                 i = int(r["Dispatch_Id"])
                 d[i] = d.get(i, 0.0) + float(r["Counter_Value"])
@@ -170,7 +175,7 @@ def main(argv=None):
     t.add_argument("copy_write_csv")
     t.add_argument("--kernel", required=True)
     t.add_argument("--copy-kernel", default="")
-    t.add_argument("--source", required=True)
+    t.add_argument("--source", required=True, nargs="+")
     t.add_argument("--algorithmic-bytes", type=int, required=True)
     t.add_argument("--reduce", choices=["median", "mean"], default="median")
     t.add_argument("--title", default="")

@@ -44,6 +44,19 @@ def test_bench_traffic_is_tied_to_the_kernel_source(tmp_path, monkeypatch):
                                   "traffic_over_algorithmic") is None
 
 
+def test_bench_traffic_names_kernels_of_its_sources():
+    import re
+
+    import bench
+    for path, sources in ((bench.TRAFFIC_FILE, bench.TRAFFIC_SOURCE),
+                          (bench.DECODE_TRAFFIC_FILE, bench.DECODE_TRAFFIC_SOURCE)):
+        named = re.search(r"^kernel: (.*)$", open(path).read(), re.M).group(1)
+        text = "".join(open(f).read() for f in sources)
+        for kernel in named.split("|"):
+            name = kernel.split("<")[0]
+            assert re.search(rf"__global__[^;{{]*\b{name}\(", text), (path, name)
+
+
 def test_entry_module_has_build_and_smoke():
     import __graft_entry__ as g
     assert callable(g.build) and callable(g.smoke)
