@@ -14,6 +14,8 @@
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <algorithm>
+#include <array>
 #include <initializer_list>
 #include <string>
 
@@ -134,21 +136,34 @@ int32_t bits_4_or_8(PyObject* o) {
 at::ScalarType code_dtype(int32_t bits) { return bits == 4 ? at::kByte : at::kChar; }
 int32_t code_bits(PyObject* bits) { return equals(bits, 4) ? 4 : 8; }
 
-// An output: the caller's tensor after its checks, or a new one.
+// The interpreter lock released for a scope, also when an exception leaves it.
+class Unlocked {
+ public:
+  Unlocked() : state_(PyEval_SaveThread()) {}
+  ~Unlocked() { PyEval_RestoreThread(state_); }
+  Unlocked(const Unlocked&) = delete;
+
+ private:
+  PyThreadState* state_;
+};
+
+// An output: the caller's tensor after its checks, or a new one (allocate).
 struct Out {
-  PyObject* o;   // a new reference
+  PyObject* o = nullptr;   // a new reference
   at::Tensor t;
-  Out(PyObject* given, const char* name, at::ScalarType dtype, std::initializer_list<int64_t> shape,
-      const at::Tensor& like) {
+  std::array<int64_t, 2> shape{};
+  int dims;
+  at::TensorOptions options;
+  Out(PyObject* given, const char* name, at::ScalarType dtype, std::initializer_list<int64_t> s,
+      const at::Tensor& like)
+      : dims((int)s.size()) {
     if (given != Py_None) {
-      t = tensor_of(given, name, dtype, shape);
+      t = tensor_of(given, name, dtype, s);
       Py_INCREF(given);
       o = given;
     } else {
-      t = at::empty(at::IntArrayRef(shape.begin(), shape.size()),
-                    at::TensorOptions().dtype(dtype).device(like.device()));
-      o = THPVariable_Wrap(t);
-      if (!o) throw Raised{};
+      std::copy(s.begin(), s.end(), shape.begin());
+      options = at::TensorOptions().dtype(dtype).device(like.device());
     }
   }
   Out(const Out&) = delete;
@@ -161,6 +176,25 @@ struct Out {
     return r;
   }
 };
+
+// Allocates the outputs that the caller did not pass.  Without the interpreter
+// lock: an allocation may wait for the device.
+template <typename... O>
+void allocate(O&... outs) {
+  if ((outs.o && ...)) return;
+  {
+    Unlocked unlocked;
+    const auto one = [](Out& out) {
+      if (!out.o) out.t = at::empty(at::IntArrayRef(out.shape.data(), out.dims), out.options);
+    };
+    (one(outs), ...);
+  }
+  const auto wrap = [](Out& out) {
+    if (!out.o) out.o = THPVariable_Wrap(out.t);
+    if (!out.o) throw Raised{};
+  };
+  (wrap(outs), ...);
+}
 
 template <typename T = void>
 T* ptr(const at::Tensor& t) { return static_cast<T*>(t.data_ptr()); }
@@ -176,17 +210,6 @@ void* stream_of(const at::Tensor& t) {
   if (!p && PyErr_Occurred()) throw Raised{};
   return p;
 }
-
-// The interpreter lock released for a scope, also when an exception leaves it.
-class Unlocked {
- public:
-  Unlocked() : state_(PyEval_SaveThread()) {}
-  ~Unlocked() { PyEval_RestoreThread(state_); }
-  Unlocked(const Unlocked&) = delete;
-
- private:
-  PyThreadState* state_;
-};
 
 // Calls the C entry f(args..., stream) on the current stream of t's device,
 // without the interpreter lock, and raises on a nonzero status.  The arguments,
@@ -239,6 +262,7 @@ PyObject* rotate_quant(PyObject* const* a) {
   const int32_t bits = bits_4_or_8(a[2]);
   Out codes(a[3], "codes", code_dtype(bits), {M, bits == 4 ? K / 2 : K}, x);
   Out scales(a[4], "scales", at::kFloat, {M}, x);
+  allocate(codes, scales);
   const at::Tensor* signs = signs_of(a[5], K, x);
   const int32_t h = integer32(a[1]);
   if (!signs)
@@ -256,6 +280,7 @@ PyObject* rotate_quant_fp6(PyObject* const* a) {
   const int64_t M = x.size(0), K = x.size(1);
   Out out(a[2], "out", at::kByte, {fp6_bytes(M, K)}, x);
   Out scales(a[3], "scales", at::kFloat, {M}, x);
+  allocate(out, scales);
   const at::Tensor* signs = signs_of(a[4], K, x);
   const int32_t h = integer32(a[1]);
   if (!signs)
@@ -276,6 +301,7 @@ PyObject* rotate_quant_range(PyObject* const* a) {
   Out codes(a[3], "codes", code_dtype(cb), {M, cb == 4 ? K / 2 : K}, x);
   Out scales(a[4], "scales", at::kFloat, {M}, x);
   Out zeros(a[5], "zeros", at::kInt, {M}, x);
+  allocate(codes, scales, zeros);
   const int32_t h = integer32(a[1]), bits = integer32(a[2]);
   call("dptq_rotate_quant_range", x, dptq_rotate_quant_range, ptr(x), M, K, h, bits, codes.ptr(),
        scales.ptr<float>(), zeros.ptr<int32_t>());
@@ -303,6 +329,7 @@ PyObject* qlinear(PyObject* const* a) {
   const at::Tensor& as = tensor_of(a[1], "a_scales", at::kFloat, {g.M});
   const at::Tensor& ws = tensor_of(a[4], "w_scales", at::kFloat, {g.N});
   Out y(a[5], "y", at::kHalf, {g.M, g.N}, g.codes);
+  allocate(y);
   const int32_t kernel = integer32(a[6]);
   if (kernel == DPTQ_GEMM_AUTO)
     call("dptq_qlinear", g.codes, dptq_qlinear, ptr(g.codes), ptr<float>(as), g.M, g.K, bits,
@@ -319,6 +346,7 @@ PyObject* qlinear_a8(PyObject* const* a) {
   const at::Tensor& as = tensor_of(a[1], "a_scales", at::kFloat, {g.M});
   const at::Tensor& ws = tensor_of(a[3], "w_scales", at::kFloat, {g.N});
   Out y(a[4], "y", at::kHalf, {g.M, g.N}, g.codes);
+  allocate(y);
   const int32_t kernel = integer32(a[5]);
   call("dptq_qlinear_a8", g.codes, dptq_qlinear_a8, ptr(g.codes), ptr<float>(as), g.M, g.K, ptr<uint8_t>(g.w),
        ptr<float>(ws), g.N, y.ptr(), kernel);
@@ -340,6 +368,7 @@ PyObject* qlinear_decode_native(PyObject* const* a) {
   const at::Tensor& as = tensor_of(a[1], "a_scales", at::kFloat, {M});
   const at::Tensor& ws = tensor_of(a[4], "w_scales", at::kFloat, {N});
   Out y(a[5], "y", at::kHalf, {M, N}, codes);
+  allocate(y);
   call("dptq_qlinear_decode_native", codes, dptq_qlinear_decode_native, ptr(codes), ptr<float>(as), M, K,
        bits, ptr<uint8_t>(w), ptr<float>(ws), N, y.ptr(), nullptr);
   return y.release();
@@ -353,6 +382,7 @@ PyObject* qlinear_fp6(PyObject* const* a) {
   const at::Tensor& as = tensor_of(a[1], "a_scales", at::kFloat, {M});
   const at::Tensor& ws = tensor_of(a[3], "w_scales", at::kFloat, {N});
   Out y(a[7], "y", at::kHalf, {M, N}, a6);
+  allocate(y);
   call("dptq_qlinear_fp6", a6, dptq_qlinear_fp6, ptr<uint8_t>(a6), ptr<float>(as), M, K, ptr<uint8_t>(w6),
        ptr<float>(ws), N, y.ptr(), nullptr);
   return y.release();
@@ -371,6 +401,7 @@ PyObject* qlinear_decode_fused(PyObject* const* a) {
   Out y(a[5], "y", at::kHalf, {M, N}, x);
   Out codes(a[6], "codes", code_dtype(cb), {M, cb == 4 ? K / 2 : K}, x);
   Out scales(a[7], "scales", at::kFloat, {M}, x);
+  allocate(y, codes, scales);
   const int32_t h = integer32(a[1]), bits = integer32(a[2]), mode = integer32(a[8]);
   call("dptq_qlinear_decode_fused", x, dptq_qlinear_decode_fused, ptr(x), M, K, h, bits, ptr<uint8_t>(w),
        ptr<float>(ws), N, y.ptr(), codes.ptr(), scales.ptr<float>(), mode);
@@ -393,6 +424,7 @@ PyObject* qlinear_range(PyObject* const* a) {
   const at::Tensor& ws = tensor_of(a[5], "w_scales", at::kFloat, {N});
   const at::Tensor& sums = tensor_of(a[6], "w_sums", at::kInt, {N});
   Out y(a[7], "y", at::kHalf, {M, N}, codes);
+  allocate(y);
   const int32_t bits = integer32(a[3]);
   call("dptq_qlinear_range", codes, dptq_qlinear_range, ptr(codes), ptr<float>(s), ptr<int32_t>(z), M, K,
        bits, ptr<uint8_t>(w), ptr<float>(ws), ptr<int32_t>(sums), N, y.ptr());
@@ -409,6 +441,7 @@ PyObject* residual_dynamics(PyObject* const* a) {
   Out jr(a[5], "jr", at::kFloat, {T}, x);
   Out snr(a[6], "snr", at::kFloat, {T}, x);
   Out means(a[7], "means", at::kDouble, {2}, x);
+  allocate(jr, snr, means);
   const int32_t h = integer32(a[2]);
   PyObject* f = PyNumber_Float(a[4]);
   if (!f) throw Raised{};
@@ -429,6 +462,7 @@ PyObject* kv_quant(PyObject* const* a) {
   Out codes(a[2], "codes", at::kByte, {T, D / 2}, kv);
   Out scales(a[3], "scales", at::kFloat, {T, D / group}, kv);
   Out mins(a[4], "mins", at::kFloat, {T, D / group}, kv);
+  allocate(codes, scales, mins);
   const int32_t g = integer32(a[1]);
   call("dptq_kv_quant", kv, dptq_kv_quant, ptr(kv), T, D, g, codes.ptr<uint8_t>(), scales.ptr<float>(),
        mins.ptr<float>());
@@ -444,6 +478,7 @@ PyObject* kv_dequant(PyObject* const* a) {
   const at::Tensor& scales = tensor_of(a[1], "scales", at::kFloat, {T, D / group});
   const at::Tensor& mins = tensor_of(a[2], "mins", at::kFloat, {T, D / group});
   Out out(a[4], "out", at::kHalf, {T, D}, codes);
+  allocate(out);
   const int32_t g = integer32(a[3]);
   call("dptq_kv_dequant", codes, dptq_kv_dequant, ptr<uint8_t>(codes), ptr<float>(scales), ptr<float>(mins),
        T, D, g, out.ptr());

@@ -1,6 +1,7 @@
 """The argument checks of the Python binding's per-call functions: what they
 refuse, with which error, and that buffers passed in are the ones returned."""
 
+import os
 import subprocess
 import sys
 
@@ -103,6 +104,54 @@ def test_numbers_accepted_and_refused():
         "ValueError", "TypeError", "TypeError", "DptqError 1", "DptqError 1", "ValueError", "DptqError 1",
         "TypeError", "TypeError", "TypeError", "DptqError 1", "TypeError", "TypeError", "ValueError",
         "DptqError 1"], r.stdout
+
+
+# An allocator that counts the allocations made with the interpreter lock held.
+_ALLOCATOR = r"""
+#include <sys/types.h>
+extern "C" {
+int hipMalloc(void**, size_t);
+int hipFree(void*);
+int PyGILState_Check(void);
+int held = 0, calls = 0;
+void* counting_malloc(ssize_t size, int, void*) {
+  void* p = nullptr;
+  ++calls;
+  held += PyGILState_Check();
+  return hipMalloc(&p, size) == 0 ? p : nullptr;
+}
+void counting_free(void* p, ssize_t, int, void*) { (void)hipFree(p); }
+}
+"""
+_COUNT = """
+import ctypes, sys, torch, paper_2606_12487_amd as dptq
+a = torch.cuda.memory.CUDAPluggableAllocator(sys.argv[1], "counting_malloc", "counting_free")
+torch.cuda.memory.change_current_allocator(a)
+L = ctypes.CDLL(sys.argv[1])
+held, calls = (ctypes.c_int.in_dll(L, n) for n in ("held", "calls"))
+x = torch.zeros((3, 128), dtype=torch.float16, device="cuda")
+w = torch.zeros((16, 64), dtype=torch.uint8, device="cuda")
+ws = torch.zeros((16,), device="cuda")
+dptq.rotate_quant(x, 128, 4)   # loads the binding
+held.value = calls.value = 0
+c, s = dptq.rotate_quant(x, 128, 4)
+y = dptq.qlinear(c, s, 4, w, ws)
+kv = dptq.kv_quant(x)
+torch.cuda.synchronize()
+print(calls.value, held.value)
+"""
+
+
+@pytest.mark.gpu
+def test_outputs_are_allocated_without_the_interpreter_lock(tmp_path):
+    src, lib = tmp_path / "alloc.cpp", tmp_path / "alloc.so"
+    src.write_text(_ALLOCATOR)
+    hip = os.path.join(os.path.dirname(torch.__file__), "lib")
+    subprocess.run(["g++", "-shared", "-fPIC", str(src), "-o", str(lib), "-L" + hip, "-lamdhip64",
+                    "-Wl,-rpath," + hip, "-Wl,--unresolved-symbols=ignore-all"], check=True, timeout=60)
+    r = subprocess.run([sys.executable, "-c", _COUNT, str(lib)], capture_output=True, text=True, timeout=110)
+    assert r.returncode == 0, (r.stdout, r.stderr[-2000:])
+    assert r.stdout.split() == ["6", "0"], r.stdout
 
 
 @pytest.mark.gpu
