@@ -262,9 +262,12 @@ inline double decode_ksplit_us(int64_t M, int64_t N, int K, int bits, int cus) {
 // decide (4 bits: M = 1, N = 2560, K = 14336 6.5 us in registers against 7.6 us, M =
 // 1, N = 28672, K = 4096 11.6 against 13.7, M = 16, N = K = 8192 10.1 against 8.9),
 // but for short rows of many channels, which the K-split kernel takes (M = 1, N =
-// 43008, K = 768: 8.1 against 9.5 us), and long rows that the register kernel
-// streams eight chunks at a time at 4 bits (M = 1, N = 1024, K = 28672: 9.4
-// against 11.4 us, N = 4096, K = 14336 7.5 against 8.0).
+// 43008, K = 768: 8.1 against 9.5 us), and two kinds of long 4-bit rows that the
+// register kernel takes: where it streams eight chunks at a time (M = 1, N = 1024, K
+// = 28672: 9.4 against 11.4 us, N = 4096, K = 14336 7.5 against 8.0), and up to eight
+// tokens of K > 16384 on at most eight blocks a compute unit, if the last round of
+// its workgroups is 85% full or the only one (M = 8, K = 28672, N = 8192: 22.9
+// against 24.1 us; a quarter full, N = 5120: 21.2 against 17.1).
 inline bool decode_in_regs(int64_t M, int64_t N, int K, int bits, bool decode_layout, int cus) {
   const int64_t nb = N / 16;
   const bool many = nb > 2 * (int64_t)cus;
@@ -273,7 +276,11 @@ inline bool decode_in_regs(int64_t M, int64_t N, int K, int bits, bool decode_la
   if (bits == 8 && K <= 384 && nb > 4 * (int64_t)cus) return true;
   if (!decode_layout) return false;
   if (K < 2048 && many) return false;
-  if (bits == 4 && N >= 1024 && decode_batch(M, N, K, 1, cus) == 8) return true;
+  if (bits == 4 && N >= 1024) {
+    if (decode_batch(M, N, K, 1, cus) == 8) return true;
+    const int64_t rounds = ceil_div(nb, cus);
+    if (M <= 8 && K > 16384 && rounds <= 8 && (rounds == 1 || 20 * nb >= 17 * cus * rounds)) return true;
+  }
   return decode_regs_us(M, N, K, bits, cus) < 1.01 * decode_ksplit_us(M, N, K, bits, cus);
 }
 

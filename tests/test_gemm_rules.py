@@ -76,10 +76,10 @@ def test_decode_shapes_of_the_register_kernel(routes):
     regs = ["decode 1 28672 128 4 0", "decode 8 4096 384 8 0", "decode 16 6144 384 4 0",
             "decode 1 2560 14336 4 1", "decode 2 1024 28672 4 1", "decode 4 28672 4096 4 1",
             "decode 2 11008 3584 4 1", "decode 1 28672 4096 8 1",
-            "decode 4 20480 256 8 1"]
+            "decode 4 20480 256 8 1", "decode 8 8192 28672 4 1", "decode 6 2560 28672 4 1"]
     ksplit = ["decode 1 4096 4096 4 0", "decode 16 4096 14336 8 0", "decode 4 16384 128 8 0",
               "decode 16 8192 8192 4 1", "decode 16 4096 14336 8 1", "decode 1 5120 14336 4 1",
-              "decode 8 57344 8192 4 1"]
+              "decode 8 57344 8192 4 1", "decode 8 5120 28672 4 1", "decode 16 8192 28672 4 1"]
     got = routes(regs + ksplit)
     assert all(r.startswith("regs") for r in got[:len(regs)]), got
     assert all(r.startswith("ksplit") for r in got[len(regs):]), got
