@@ -120,6 +120,8 @@ FUSED_CASES = [
     # one row on both thread groups: segments split by parity (2 and 3 of
     # them), and three rows that do not fit two at a time
     (1, 8192, 256, 8192, 4), (1, 11008, 256, 256, 8), (3, 14336, 128, 28 * 512, 4),
+    # one row of h = 2^14: the longest segment that the automatic rule gives one launch
+    (1, 16384, 64, 16384, 4), (1, 16384, 64, 16384, 8),
 ]
 # Shapes whose rows do not fit on chip: the two-launch path only.
 TWO_LAUNCH_ONLY = [(16, 14336, 4096, 28 * 512, 8), (8, 28672, 256, 28 * 1024, 4),
